@@ -375,7 +375,7 @@ gs_status gs_init_gaussians(gs_ctx* ctx, const float* points, const float* rgb, 
  * flag.  lm_lambda > 0. */
 #define GS_BA_MAX_CAMS 65536
 typedef struct gs_ba gs_ba;
-/* BA workspace: 96 B per point and 676 B per camera of device memory,
+/* BA workspace: 160 B per point and 836 B per camera of device memory,
  * allocated once. */
 gs_status gs_ba_create(gs_ba** out, int64_t max_points, int32_t max_cams);
 gs_status gs_ba_destroy(gs_ba* ba);
