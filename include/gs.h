@@ -117,8 +117,9 @@ typedef struct {
     float alpha_max;          /* 0.99 */
     float t_min;              /* 1e-4 */
     int32_t grad_accumulate;  /* 0: gs_render_bwd overwrites Gaussian grads; 1: adds */
-    int32_t tile_order;       /* 0: natural tile order; 1: launch the raster kernels on
-                                 the tiles heaviest first: by decreasing bucket of the
+    int32_t tile_order;       /* launch order of the forward (the backward orders its tiles
+                                 by what it will walk).  0: natural tile order; 1: the
+                                 tiles heaviest first: by decreasing bucket of the
                                  list length, 16 buckets per octave (bucket of n > 0:
                                  1 + 16 floor(log2 n) + the 4 bits after n's leading
                                  bit; 0 for an empty list), any order inside a bucket;
@@ -133,9 +134,9 @@ typedef struct {
     int32_t lazy_lists;       /* 0: gs_bin_sort writes every tile list in full;
                                  1: it stops at the per-block lists and the tile list
                                  lengths, and gs_render_fwd draws each tile's list from
-                                 its block's list, writing the part it reads (up to the
-                                 batch of 64 in which the tile's last pixel stopped) to
-                                 the tile lists.  The backward reads no further than that
+                                 its block's list, writing the part it reads (to the
+                                 end of the block entries loaded when the tile's last
+                                 pixel stopped) to the tile lists.  The backward reads no further than that
                                  part; run without a forward since the bin step, it first
                                  writes the lists in full.  Images and gradients are the
                                  same bit for bit; only the unread list tails are left
