@@ -169,7 +169,8 @@ gs_status gs_ctx_create(gs_ctx** out, const gs_capacity* cap) {
     auto A = [&](hipError_t r) {
         if (e == hipSuccess) e = r;
     };
-    A(dalloc(&c.rec, (size_t)P * GS_RECORD_FLOATS));
+    // (gs_init_gaussians sorts whole leaves of 8 points, 16 B each, into it)
+    A(dalloc(&c.rec, std::max<size_t>((size_t)P * GS_RECORD_FLOATS, 32)));
     A(dalloc(&c.grad2d, (size_t)P * GS_GRAD2D_FLOATS));
     A(dalloc(&c.cnt, (size_t)P));
     A(dalloc(&c.vmu_dir, (size_t)3 * (P > 0 ? P : 1)));

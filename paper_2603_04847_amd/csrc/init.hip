@@ -10,14 +10,16 @@
 // stores each node's axis-aligned box of its points.  Because the boxes are
 // the points' own boxes and the leaves split by count, not by space, the
 // search adapts to the density: clustered scenes (dense blobs next to sparse
-// outliers) cost about the same per point as uniform ones.  Each point first
-// takes the kWin points on either side of it in the sorted order (almost
-// always near it) as candidates, which bounds its k-th distance, then walks
-// the tree depth first without a stack (left child first; after a subtree,
-// climb while on a right child, then step to the sibling) and skips every
-// box farther than the current k-th distance.  The box distance is computed
-// with the same float operations as the point distances and is monotone in
-// them, so no point nearer than the bound is ever skipped.
+// outliers) cost about the same per point as uniform ones.  A wave
+// searches for 64 consecutive points of the order at once.  It first takes its
+// own leaves and kSide on either side of them (almost always near) as
+// candidates, which bounds each point's k-th distance; it then walks the tree
+// six levels at a step, a lane testing one of a node's 64 descendants there
+// (contiguous in heap order) against the boxes of the wave's four rows of 16
+// points, and the points testing each survivor, skipping every box farther than
+// all their k-th distances.  The box distances are computed with the same float
+// operations as the point distances and are monotone in them, so no point
+// nearer than the bound is ever skipped.
 #include <math.h>
 
 #include <algorithm>
@@ -31,17 +33,28 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kMaxK = GS_INIT_MAX_K;
 constexpr int kLeaf = 8;           // points per leaf
-constexpr int kWin = 8;            // sorted neighbours taken on each side first
+constexpr int kSide = 2;           // leaves on either side of a wave's own taken first
 constexpr int kBoxBlocks = 1024;   // blocks of the bounding-box reduction
 constexpr int kUpBlock = 256;      // nodes per block in the bottom-up box pass
 constexpr float kSMin = 1e-7f;     // smallest scale (coincident points)
 
-static_assert(2 * kWin >= kMaxK, "the window must hold k candidates");
+// up to here a wave takes every leaf first, and there is no tree
+constexpr int kNoTree = (kSide + 1) * kLeaf;
 
 // Morton cells: origin and 1024 / (side of the bounding cube)
 struct Grid {
     float ox, oy, oz, ih;
 };
+
+// the wave's least lo and greatest hi, in every lane
+__device__ __forceinline__ void wave_box(float (&lo)[3], float (&hi)[3]) {
+#pragma unroll
+    for (int a = 0; a < 3; a++)
+        for (int off = 32; off > 0; off >>= 1) {
+            lo[a] = fminf(lo[a], __shfl_xor(lo[a], off, kWave));
+            hi[a] = fmaxf(hi[a], __shfl_xor(hi[a], off, kWave));
+        }
+}
 
 // per block: min and max of x, y, z
 __global__ __launch_bounds__(kBlock) void k_box_partial(const float* __restrict__ pts, int n,
@@ -56,12 +69,7 @@ __global__ __launch_bounds__(kBlock) void k_box_partial(const float* __restrict_
             hi[a] = fmaxf(hi[a], v);
         }
     }
-#pragma unroll
-    for (int a = 0; a < 3; a++)
-        for (int off = 32; off > 0; off >>= 1) {
-            lo[a] = fminf(lo[a], __shfl_xor(lo[a], off, kWave));
-            hi[a] = fmaxf(hi[a], __shfl_xor(hi[a], off, kWave));
-        }
+    wave_box(lo, hi);
     const int w = threadIdx.x / kWave;
     if (__lane_id() == 0)
         for (int a = 0; a < 3; a++) {
@@ -78,15 +86,17 @@ __global__ __launch_bounds__(kBlock) void k_box_partial(const float* __restrict_
 }
 
 // The Morton grid: 1024 cells per axis over the bounding cube (the order only
-// serves locality; the search does not depend on the cells).
-__global__ void k_grid(const float* __restrict__ part, int nb, Grid* __restrict__ g) {
-    if (threadIdx.x != 0) return;
+// serves locality; the search does not depend on the cells).  One wave.
+__global__ __launch_bounds__(kWave) void k_grid(const float* __restrict__ part, int nb, Grid* __restrict__ g) {
     float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int b = 0; b < nb; b++)
+    for (int b = threadIdx.x; b < nb; b += kWave)
+#pragma unroll
         for (int a = 0; a < 3; a++) {
             lo[a] = fminf(lo[a], part[6 * b + a]);
             hi[a] = fmaxf(hi[a], part[6 * b + 3 + a]);
         }
+    wave_box(lo, hi);
+    if (threadIdx.x != 0) return;
     const float e = fmaxf(hi[0] - lo[0], fmaxf(hi[1] - lo[1], hi[2] - lo[2]));
     Grid G;
     G.ox = lo[0];
@@ -125,46 +135,34 @@ __global__ __launch_bounds__(kBlock) void k_cell_keys(const float* __restrict__ 
     vals[i] = (uint32_t)i;
 }
 
-// points in sorted order (x, y, z, -)
+// points in sorted order (x, y, z, -), the last leaf filled up with points that
+// are near nothing
 __global__ __launch_bounds__(kBlock) void k_gather(const float* __restrict__ pts, int n,
                                                    const uint32_t* __restrict__ vals,
                                                    float4* __restrict__ sp) {
     const int j = blockIdx.x * kBlock + threadIdx.x;
-    if (j >= n) return;
+    if (j >= (n + kLeaf - 1) / kLeaf * kLeaf) return;
+    if (j >= n) {
+        sp[j] = make_float4(INFINITY, INFINITY, INFINITY, 0.f);
+        return;
+    }
     const int64_t q = vals[j];
     sp[j] = make_float4(pts[3 * q], pts[3 * q + 1], pts[3 * q + 2], 0.f);
 }
 
-// the K smallest squared distances seen, ascending (K >= k: the first k of
-// them are the k nearest)
+// The k <= K smallest squared distances seen, ascending, in the last k places
+// (the first K - k hold -inf, so the k-th is always the last).
 template <int K>
 struct TopK {
     float d[K];
-    int cnt;
-    __device__ void init() {
-#pragma unroll
-        for (int i = 0; i < K; i++) d[i] = INFINITY;
-        cnt = 0;
-    }
-    __device__ void push(float v) {
-        if (!(v < d[K - 1])) return;
-        float x = v;
+    // v: not a NaN
+    __device__ __forceinline__ void push(float v) {
 #pragma unroll
         for (int i = 0; i < K; i++) {
-            if (x < d[i]) {
-                const float t = d[i];
-                d[i] = x;
-                x = t;
-            }
+            const float t = fminf(d[i], v);
+            v = fmaxf(d[i], v);
+            d[i] = t;
         }
-        cnt = min(cnt + 1, K);
-    }
-    // the i-th smallest (i < K), by selects (no dynamic register index)
-    __device__ float at(int i) const {
-        float r = d[0];
-#pragma unroll
-        for (int q = 1; q < K; q++) r = q == i ? d[q] : r;
-        return r;
     }
 };
 
@@ -244,48 +242,131 @@ __device__ __forceinline__ float box_dist2(float4 lo, float4 hi, float4 p) {
     return __builtin_fmaf(ex, ex, __builtin_fmaf(ey, ey, ez * ez));
 }
 
-// one thread per point, in sorted order; the mean of the k nearest distances
-// goes to s[original index].  With n <= 2 kWin + 1 the window holds every
-// point and there is no tree.
+// The greatest of v in each row of 16 lanes, in all of its lanes.
+__device__ __forceinline__ float row_max(float v) {
+    v = fmaxf(v, dpp_f<0xB1>(v));
+    v = fmaxf(v, dpp_f<0x4E>(v));
+    v = fmaxf(v, dpp_f<0x124>(v));  // row_ror:4
+    return fmaxf(v, dpp_f<0x128>(v));
+}
+
+// The search of a wave's 64 points (one a lane, in sorted order).
 template <int K>
-__global__ __launch_bounds__(kBlock) void k_knn(const uint32_t* __restrict__ vals,
-                                                const float4* __restrict__ sp, int n, int k,
-                                                const float4* __restrict__ tree, int NL,
-                                                float* __restrict__ s) {
-    const int j = blockIdx.x * kBlock + threadIdx.x;
-    if (j >= n) return;
-    const float4 p = sp[j];
-    const int kk = min(k, n - 1);
+struct Search {
+    const float4* __restrict__ sp;
+    const float4* __restrict__ tree;
+    int NL, nl, l0, l1;  // leaves 0 .. nl - 1 hold points; l0 .. l1 - 1 are taken
+    float4 p;
     TopK<K> best;
-    best.init();
-    const int j1 = min(n - 1, max(j - kWin, 0) + 2 * kWin);
-    const int j0 = max(0, j1 - 2 * kWin);
-    for (int i = j0; i <= j1; i++)
-        if (i != j) best.push(dist2(sp[i], p));
-    float bound = kk > 0 ? best.at(kk - 1) : 0.f;
-    if (n > 2 * kWin + 1 && bound > 0.f) {
-        int v = 1;
-        while (true) {
-            bool go = box_dist2(tree[2 * (int64_t)v], tree[2 * (int64_t)v + 1], p) <= bound;
-            if (go && v >= NL) {
-                const int a = (v - NL) * kLeaf, b = min(n, a + kLeaf);
-                for (int i = a; i < b; i++)
-                    if (i < j0 || i > j1) best.push(dist2(sp[i], p));
-                bound = best.at(kk - 1);
-                go = false;
-            }
-            if (go) {
-                v = 2 * v;
-                continue;
-            }
-            while (v & 1) v >>= 1;  // finished a right child: climb
-            if (v == 0) break;      // climbed past the root
-            v += 1;                 // the right sibling
+    bool open;                  // whether the point has anything to look for
+    float glo[4][3], ghi[4][3]; // the boxes of the wave's rows
+
+    // the largest squared distance of interest
+    __device__ __forceinline__ float bound() const { return open ? best.d[K - 1] : -1.f; }
+
+    // the 8 points of a leaf, each read by all lanes from one address; j: this
+    // lane's own place in the order, or -1 where the leaf does not hold it
+    __device__ __forceinline__ void leaf(int l, int j) {
+        const float4* o = sp + l * kLeaf;
+#pragma unroll
+        for (int i = 0; i < kLeaf; i++) {
+            const float d2 = dist2(o[i], p);
+            const bool nearer = d2 < best.d[K - 1] && l * kLeaf + i != j;  // (a NaN is not)
+            if (__ballot(nearer) != 0) best.push(nearer ? d2 : INFINITY);
         }
     }
+
+    // Node v's descendants `width` nodes of heap order wide (64, or fewer for
+    // the root's step), D such steps above the leaves: lane i tests descendant
+    // v width + i against the rows' boxes and largest bounds; the points then
+    // test each survivor.
+    template <int D>
+    __device__ __forceinline__ void visit(int v, int width) {
+        const int lane = threadIdx.x % kWave;
+        const int c0 = v * width;
+        const float rb = row_max(bound());
+        float4 lo = make_float4(INFINITY, INFINITY, INFINITY, 0.f), hi = make_float4(-INFINITY, -INFINITY, -INFINITY, 0.f);
+        if (lane < width) {
+            lo = tree[2 * (int64_t)(c0 + lane)];
+            hi = tree[2 * (int64_t)(c0 + lane) + 1];
+        }
+        bool near = false;
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const float ex = fmaxf(fmaxf(lo.x - ghi[r][0], glo[r][0] - hi.x), 0.f);
+            const float ey = fmaxf(fmaxf(lo.y - ghi[r][1], glo[r][1] - hi.y), 0.f);
+            const float ez = fmaxf(fmaxf(lo.z - ghi[r][2], glo[r][2] - hi.z), 0.f);
+            near |= __builtin_fmaf(ex, ex, __builtin_fmaf(ey, ey, ez * ez)) <= bcast(rb, 16 * r);
+        }
+        if (D == 1) {
+            const int l = c0 + lane - NL;
+            near = near && l < nl && (unsigned)(l - l0) >= (unsigned)(l1 - l0);
+        }
+        uint64_t todo = __ballot(near);
+        while (todo) {
+            const int b = __ffsll((unsigned long long)todo) - 1;
+            todo &= todo - 1;
+            const float4 l = make_float4(bcast(lo.x, b), bcast(lo.y, b), bcast(lo.z, b), 0.f);
+            const float4 h = make_float4(bcast(hi.x, b), bcast(hi.y, b), bcast(hi.z, b), 0.f);
+            if (__ballot(box_dist2(l, h, p) <= bound()) == 0) continue;
+            if constexpr (D == 1)
+                leaf(c0 + b - NL, -1);
+            else
+                visit<D - 1>(c0 + b, kWave);
+        }
+    }
+};
+
+// A wave per 64 points, in sorted order; the mean of the k nearest distances
+// goes to s[original index].  With n <= kNoTree there is no tree.
+// VALU-bound (about 14000 instructions a wave): a wave's points share the tree's
+// and the leaves' loads, and a leaf's points reach the lanes from one address.
+// 1.5M clustered points, k = 4, under the profiler: 930 us; 3800 with a thread
+// per point walking the tree by itself (its lanes on unlike nodes, a dependent
+// load each step); 2130 with the wave's points bounded by their 16 sorted
+// neighbours and prefiltered by one box.
+template <int K, int STEPS>
+__global__ __launch_bounds__(kBlock) void k_knn(const uint32_t* __restrict__ vals,
+                                                const float4* __restrict__ sp, int n, int k,
+                                                const float4* __restrict__ tree, int NL, int levels,
+                                                float* __restrict__ s) {
+    const int j = blockIdx.x * kBlock + threadIdx.x;
+    const int w0 = __builtin_amdgcn_readfirstlane(j - threadIdx.x % kWave);  // the wave's first point
+    if (w0 >= n) return;
+    const bool mine = j < n;
+    const int nl = (n + kLeaf - 1) / kLeaf;
+    Search<K> S;
+    S.sp = sp;
+    S.tree = tree;
+    S.NL = NL;
+    S.nl = nl;
+    S.l0 = max(w0 / kLeaf - kSide, 0);
+    S.l1 = min(w0 / kLeaf + kWave / kLeaf + kSide, nl);
+    const int kk = min(k, n - 1);
+    S.p = sp[min(j, n - 1)];
+#pragma unroll
+    for (int i = 0; i < K; i++) S.best.d[i] = mine && i >= K - kk ? INFINITY : -INFINITY;
+    for (int l = S.l0; l < S.l1; l++) S.leaf(l, j);
+    // (nothing to look for when all its neighbours coincide with it)
+    S.open = mine && kk > 0 && S.best.d[K - 1] > 0.f;
+    if (n > kNoTree && __ballot(S.open) != 0) {
+        const float x[3] = {S.p.x, S.p.y, S.p.z};
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            const float lo = -row_max(S.open ? -x[a] : -INFINITY), hi = row_max(S.open ? x[a] : -INFINITY);
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                S.glo[r][a] = bcast(lo, 16 * r);
+                S.ghi[r][a] = bcast(hi, 16 * r);
+            }
+        }
+        // steps of six levels, the odd ones at the root
+        S.template visit<STEPS>(1, 1 << (levels - 6 * (STEPS - 1)));
+    }
+    if (!mine) return;
     float m = 0.f;
 #pragma unroll
-    for (int i = 0; i < K; i++) m += i < kk ? sqrtf(best.d[i]) : 0.f;
+    for (int i = 0; i < K; i++) m += i >= K - kk ? sqrtf(S.best.d[i]) : 0.f;
     m = kk > 0 ? m / (float)kk : 0.f;
     s[vals[j]] = fmaxf(m, kSMin);
 }
@@ -341,25 +422,27 @@ hipError_t launch_init_gaussians(Ctx* c, const float* pts, const float* rgb, int
     if (e != hipSuccess) return e;
     const uint32_t* vals = c->pv[side];
     // sorted points, then the tree, in the record buffer (12 floats per pair):
-    // 16 n bytes and 32 * 2 NL <= 16 n + 48 bytes (NL < 2 ceil(n / 8))
+    // 128 nl bytes and, past kNoTree points, 64 NL < 128 nl (nl = ceil(n / 8))
+    const int nl = (n + kLeaf - 1) / kLeaf;
     float4* sp = reinterpret_cast<float4*>(c->rec);
-    float4* tree = sp + n;
+    float4* tree = sp + (int64_t)nl * kLeaf;
     float* s = reinterpret_cast<float*>(c->cnt);
     hipLaunchKernelGGL(k_gather, dim3(g), dim3(kBlock), 0, st, pts, n, vals, sp);
-    int NL = 0;
-    if (n > 2 * kWin + 1) {
-        const int nl = (n + kLeaf - 1) / kLeaf;
+    int NL = 0, levels = 0;
+    if (n > kNoTree) {
         NL = 1;
-        while (NL < nl) NL *= 2;
+        while (NL < nl) NL *= 2, levels++;
         hipLaunchKernelGGL(k_leaf_box, dim3((NL + kBlock - 1) / kBlock), dim3(kBlock), 0, st, sp, n, NL,
                            tree);
         for (int m = NL / 2; m >= 1; m /= 2 * kUpBlock)
             hipLaunchKernelGGL(k_tree_up, dim3(std::max(1, m / kUpBlock)), dim3(kUpBlock), 0, st, tree, m);
     }
-    if (k <= 4)
-        hipLaunchKernelGGL(k_knn<4>, dim3(g), dim3(kBlock), 0, st, vals, sp, n, k, tree, NL, s);
-    else
-        hipLaunchKernelGGL(k_knn<kMaxK>, dim3(g), dim3(kBlock), 0, st, vals, sp, n, k, tree, NL, s);
+    const auto knn = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(g), dim3(kBlock), 0, st, vals, sp, n, k, tree, NL, levels, s);
+    };
+    const int steps = (levels + 5) / 6;  // (n <= max_pairs <= 2^26: at most 23 levels)
+    if (k <= 4) knn(steps <= 1 ? k_knn<4, 1> : steps == 2 ? k_knn<4, 2> : steps == 3 ? k_knn<4, 3> : k_knn<4, 4>);
+    else knn(steps <= 1 ? k_knn<kMaxK, 1> : steps == 2 ? k_knn<kMaxK, 2> : steps == 3 ? k_knn<kMaxK, 3> : k_knn<kMaxK, 4>);
     const float lg = logf(opacity / (1.f - opacity));
     const int K = (sh_degree + 1) * (sh_degree + 1);
     hipLaunchKernelGGL(k_init_write, dim3(g), dim3(kBlock), 0, st, pts, rgb, n, K, lg, s, means,
