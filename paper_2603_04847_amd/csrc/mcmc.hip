@@ -6,9 +6,14 @@
 //
 // Draws are exact integer arithmetic: each live Gaussian weighs
 // floor(o 2^24) (o from the logit in double), the weights' inclusive prefix
-// sums are 64-bit (a block pass, one workgroup for the block totals, a block
-// pass again), and dead Gaussian j takes the first index whose prefix exceeds
-// floor(u_j W), found by binary search.
+// sums are 64-bit (a block pass, one workgroup for the block totals), and dead
+// Gaussian j takes the first index whose prefix exceeds floor(u_j W), found by
+// binary search over the blocks, then in one.
+//
+// What moves is 59 rows of parameters and 118 of moments (SH degree 3), a
+// fifth of their words at random places: the rows are taken one after another
+// by the whole chip, so that a row's gathers find it in the cache and each line
+// is written once, and the dead are listed in order, so that every lane has one.
 #include <math.h>
 
 #include <algorithm>
@@ -23,12 +28,12 @@ constexpr int kBlock = 1024;      // items (and threads) per block of the prefix
 constexpr int kMaxCopies = 51;    // copies counted in the opacity and scale rule
 constexpr double kWeightScale = 16777216.0;  // 2^24
 
-struct McState {
-    float* p[5];
-    float* m[5];
-    float* v[5];
-    int rows[5];
-    int N;
+// Rows of N floats: of the parameters, or of both moments.
+constexpr int kMaxRows = 11 + 3 * 16;
+template <int MAX>
+struct Rows {
+    float* p[MAX];
+    int n;
 };
 
 __device__ __forceinline__ double opacity_of(float logit) { return 1.0 / (1.0 + exp(-(double)logit)); }
@@ -52,126 +57,186 @@ __device__ __forceinline__ uint64_t block_incl_scan_u64(uint64_t v, uint64_t* s,
     return v + before;
 }
 
-// per item: its weight; per block: the sum
+// threads of the wave below this one that `on` holds for
+__device__ __forceinline__ int rank_in(uint64_t on) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(on >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)on, 0u));
+}
+
+// The threads of the block that `on` holds for, listed in order in s_list
+// (their thread indices); returns their number.
+__device__ __forceinline__ int block_list(bool on, int* s_list, int* s_n) {
+    const int w = threadIdx.x / kWave;
+    const uint64_t bal = __ballot(on);
+    if (threadIdx.x % kWave == 0) s_n[w] = __popcll(bal);
+    __syncthreads();
+    int before = 0, all = 0;
+    for (int q = 0; q < kBlock / kWave; q++) {
+        if (q < w) before += s_n[q];
+        all += s_n[q];
+    }
+    if (on) s_list[before + rank_in(bal)] = threadIdx.x;
+    __syncthreads();
+    return all;
+}
+
+// per item: its weight's prefix within the block, no draws yet; per block: the
+// weights' sum and the number of dead
 __global__ __launch_bounds__(kBlock) void k_mc_weights(const float* __restrict__ logit, int N, float t_dead,
-                                                       uint64_t* __restrict__ cdf,
-                                                       uint64_t* __restrict__ bsum) {
+                                                       uint64_t* __restrict__ cdf, uint64_t* __restrict__ bsum,
+                                                       uint64_t* __restrict__ bdead,
+                                                       uint32_t* __restrict__ count) {
     __shared__ uint64_t s[kBlock / kWave];
+    __shared__ int s_d[kBlock / kWave];
     const int i = blockIdx.x * kBlock + threadIdx.x;
     uint64_t w = 0;
+    bool dead = false;
     if (i < N) {
         const double o = opacity_of(logit[i]);
-        if (o > (double)t_dead) w = (uint64_t)floor(o * kWeightScale);
+        dead = !(o > (double)t_dead);
+        if (!dead) w = (uint64_t)floor(o * kWeightScale);
     }
+    const uint64_t bal = __ballot(dead);
+    if (threadIdx.x % kWave == 0) s_d[threadIdx.x / kWave] = __popcll(bal);
     uint64_t tot;
-    const uint64_t inc = block_incl_scan_u64(w, s, tot);
-    if (i < N) cdf[i] = inc;  // the block-local prefix; the block offset is added below
-    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
-}
-
-// one workgroup: exclusive prefix of the block sums, the total last
-__global__ __launch_bounds__(kBlock) void k_mc_block_offsets(uint64_t* __restrict__ bsum, int nb) {
-    __shared__ uint64_t s[kBlock / kWave];
-    uint64_t carry = 0;
-    for (int base = 0; base < nb; base += kBlock) {
-        const int b = base + threadIdx.x;
-        const uint64_t v = b < nb ? bsum[b] : 0;
-        uint64_t tot;
-        const uint64_t inc = block_incl_scan_u64(v, s, tot);
-        if (b < nb) bsum[b] = carry + inc - v;
-        carry += tot;
-    }
-    if (threadIdx.x == 0) bsum[nb] = carry;
-}
-
-__global__ __launch_bounds__(kBlock) void k_mc_cdf(uint64_t* __restrict__ cdf, int N,
-                                                   const uint64_t* __restrict__ bsum,
-                                                   uint32_t* __restrict__ count) {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
+    const uint64_t inc = block_incl_scan_u64(w, s, tot);  // (its barriers also order s_d)
     if (i < N) {
-        cdf[i] += bsum[blockIdx.x];
+        cdf[i] = inc;
         count[i] = 0u;
     }
+    if (threadIdx.x == 0) {
+        int d = 0;
+        for (int q = 0; q < kBlock / kWave; q++) d += s_d[q];
+        bsum[blockIdx.x] = tot;
+        bdead[blockIdx.x] = (uint64_t)d;
+    }
 }
 
-// each dead Gaussian draws its source
+// one workgroup: exclusive prefixes of the block sums, the totals last
+__global__ __launch_bounds__(kBlock) void k_mc_block_offsets(uint64_t* __restrict__ bsum,
+                                                             uint64_t* __restrict__ bdead, int nb,
+                                                             int32_t* __restrict__ n_moved) {
+    __shared__ uint64_t s[kBlock / kWave];
+    uint64_t carry[2] = {0, 0};
+    for (int base = 0; base < nb; base += kBlock) {
+        const int b = base + threadIdx.x;
+#pragma unroll
+        for (int a = 0; a < 2; a++) {
+            uint64_t* x = a ? bdead : bsum;
+            const uint64_t v = b < nb ? x[b] : 0;
+            uint64_t tot;
+            const uint64_t inc = block_incl_scan_u64(v, s, tot);
+            if (b < nb) x[b] = carry[a] + inc - v;
+            carry[a] += tot;
+        }
+    }
+    if (threadIdx.x != 0) return;
+    if (carry[0] == 0) carry[1] = 0;  // no live Gaussian: nothing moves
+    bsum[nb] = carry[0];
+    bdead[nb] = carry[1];
+    if (n_moved) *n_moved = (int32_t)carry[1];
+}
+
+// the first place in [0, n) where a[place] > v (n if there is none)
+__device__ __forceinline__ int first_above(const uint64_t* __restrict__ a, int n, uint64_t v) {
+    int lo = 0, hi = n;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (a[mid] > v) hi = mid;
+        else lo = mid + 1;
+    }
+    return lo;
+}
+
+// Each dead Gaussian draws its source; the dead and their sources are listed
+// in order.
 __global__ __launch_bounds__(kBlock) void k_mc_draw(const float* __restrict__ logit, int N, float t_dead,
                                                     const float* __restrict__ u,
                                                     const uint64_t* __restrict__ cdf,
-                                                    const uint64_t* __restrict__ total_p,
+                                                    const uint64_t* __restrict__ bsum,
+                                                    const uint64_t* __restrict__ bdead, int nb,
                                                     int32_t* __restrict__ src, uint32_t* __restrict__ count,
-                                                    int32_t* __restrict__ n_moved) {
-    __shared__ int s_cnt;
-    if (threadIdx.x == 0) s_cnt = 0;
-    __syncthreads();
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < N) {
-        const uint64_t W = *total_p;
-        int s = -1;
-        if (W > 0 && !(opacity_of(logit[i]) > (double)t_dead)) {
-            const uint64_t tv = (uint64_t)floor((double)u[i] * (double)W);
-            int lo = 0, hi = N;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (cdf[mid] > tv) hi = mid;
-                else lo = mid + 1;
-            }
-            s = min(lo, N - 1);
-            atomicAdd(&count[s], 1u);
-            atomicAdd(&s_cnt, 1);
-        }
-        src[i] = s;
+                                                    int2* __restrict__ list) {
+    __shared__ int s_list[kBlock], s_n[kBlock / kWave];
+    const int i0 = blockIdx.x * kBlock, i = i0 + threadIdx.x;
+    const uint64_t W = bsum[nb];
+    const bool dead = i < N && W > 0 && !(opacity_of(logit[i]) > (double)t_dead);
+    if (i < N && !dead) src[i] = -1;
+    const int nd = block_list(dead, s_list, s_n);
+    if ((int)threadIdx.x >= nd) return;
+    const int d = i0 + s_list[threadIdx.x];
+    const uint64_t tv = (uint64_t)floor((double)u[d] * (double)W);
+    const int b = first_above(bsum + 1, nb, tv);  // bsum[b + 1]: the prefix to the end of block b
+    int s = N - 1;
+    if (b < nb) {
+        const int n = min(kBlock, N - b * kBlock);
+        s = min(b * kBlock + first_above(cdf + (int64_t)b * kBlock, n, tv - bsum[b]), N - 1);
     }
-    __syncthreads();
-    if (threadIdx.x == 0 && s_cnt && n_moved) atomicAdd(n_moved, s_cnt);
+    atomicAdd(&count[s], 1u);
+    src[d] = s;
+    list[bdead[blockIdx.x] + threadIdx.x] = make_int2(d, s);
 }
 
-__device__ __forceinline__ void reset_moments(const McState& st, int i) {
-#pragma unroll
-    for (int q = 0; q < 5; q++)
-        for (int r = 0; r < st.rows[q]; r++) {
-            st.m[q][(int64_t)r * st.N + i] = 0.f;
-            st.v[q][(int64_t)r * st.N + i] = 0.f;
-        }
-}
-
-// sources: the opacity and scale of their n copies
-__global__ __launch_bounds__(256) void k_mc_sources(McState st, const uint32_t* __restrict__ count) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= st.N || count[i] == 0u) return;
-    const int n = (int)min(count[i] + 1u, (uint32_t)kMaxCopies);
-    const double o = opacity_of(st.p[3][i]);
+// Sources: the opacity and scale of their n copies,
+//   o' = 1 - (1 - o)^(1/n),  scale *= o / sum_{i=1..n} sum_{k<i} C(i-1, k) (-1)^k o'^(k+1) / sqrt(k+1),
+// the double sum taken as sum_{k<n} C(n, k+1) (-1)^k o'^(k+1) / sqrt(k+1) (the
+// binomials sum up a diagonal, and are exact in double to n = 51).  Per 64
+// items, a word of which of them moved (dead or source).
+__global__ __launch_bounds__(kBlock) void k_mc_sources(float* __restrict__ logit, float* __restrict__ ls, int N,
+                                                       const uint32_t* __restrict__ count,
+                                                       const int32_t* __restrict__ src,
+                                                       uint64_t* __restrict__ moved) {
+    __shared__ int s_list[kBlock], s_n[kBlock / kWave];
+    __shared__ double s_rs[kMaxCopies];
+    const int i0 = blockIdx.x * kBlock, i = i0 + threadIdx.x;
+    if (threadIdx.x < kMaxCopies) s_rs[threadIdx.x] = rsqrt((double)(threadIdx.x + 1));
+    const bool source = i < N && count[i] != 0u;
+    const uint64_t mv = __ballot(source || (i < N && src[i] >= 0));
+    if (threadIdx.x % kWave == 0 && i < N) moved[i / kWave] = mv;
+    const int ns = block_list(source, s_list, s_n);
+    if ((int)threadIdx.x >= ns) return;
+    const int j = i0 + s_list[threadIdx.x];
+    const int n = (int)min(count[j] + 1u, (uint32_t)kMaxCopies);
+    const double o = opacity_of(logit[j]);
     const double op = 1.0 - pow(1.0 - o, 1.0 / n);
-    double denom = 0.0;
-    for (int a = 1; a <= n; a++) {
-        double c = 1.0, pw = op;  // C(a-1, k), op^(k+1)
-        for (int k = 0; k <= a - 1; k++) {
-            denom += ((k & 1) ? -c : c) * pw * rsqrt((double)(k + 1));
-            c = c * (double)(a - 1 - k) / (double)(k + 1);
-            pw *= op;
-        }
+    double denom = 0.0, c = 1.0, pw = op;
+    for (int k = 0; k < n; k++) {
+        c = c * (double)(n - k) / (double)(k + 1);  // C(n, k + 1)
+        denom += ((k & 1) ? -c : c) * pw * s_rs[k];
+        pw *= op;
     }
     const double lf = log(o / denom);
-    st.p[3][i] = (float)log(op / (1.0 - op));
+    logit[j] = (float)log(op / (1.0 - op));
 #pragma unroll
     for (int a = 0; a < 3; a++) {
-        float& ls = st.p[1][(int64_t)a * st.N + i];
-        ls = (float)((double)ls + lf);
+        float& l = ls[(int64_t)a * N + j];
+        l = (float)((double)l + lf);
     }
-    reset_moments(st, i);
 }
 
-// dead Gaussians: copies of their (updated) source
-__global__ __launch_bounds__(256) void k_mc_copy(McState st, const int32_t* __restrict__ src) {
+// Dead Gaussians: copies of their (updated) source.  blockIdx.y is the row, so
+// the chip works within a few rows at a time (20 MB each for 5M Gaussians),
+// which the last-level cache holds: bound by the random lines the gathers take
+// from it and the partial lines written.  5M Gaussians, a fifth dead, 59 rows,
+// us by the rows a thread takes together: 1 1218, 2 1263, 4 1289, 8 1303, 16
+// 1312, all 1742; a thread per Gaussian, dead or not, walking all rows and then
+// the moments' took 2975.
+__global__ __launch_bounds__(256) void k_mc_copy(Rows<kMaxRows> rows, const int2* __restrict__ list,
+                                                 const uint64_t* __restrict__ n_dead) {
+    const int n = (int)*n_dead;
+    float* row = rows.p[blockIdx.y];
+    for (int e = blockIdx.x * 256 + threadIdx.x; e < n; e += gridDim.x * 256) {
+        const int2 ds = list[e];
+        row[ds.x] = row[ds.y];
+    }
+}
+
+// The moments of everything that moved restart at zero.  Bound by the partial
+// lines written (37% of the words at random: every line): 5M Gaussians, 118 rows
+// 916 us, a row after another; 967 eight rows to a thread.
+__global__ __launch_bounds__(256) void k_mc_zero(Rows<2 * kMaxRows> rows, int N,
+                                                 const uint64_t* __restrict__ moved) {
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= st.N) return;
-    const int s = src[i];
-    if (s < 0) return;
-#pragma unroll
-    for (int q = 0; q < 5; q++)
-        for (int r = 0; r < st.rows[q]; r++)
-            st.p[q][(int64_t)r * st.N + i] = st.p[q][(int64_t)r * st.N + s];
-    reset_moments(st, i);
+    if (i < N && (moved[i / kWave] >> (i % kWave) & 1)) rows.p[blockIdx.y][i] = 0.f;
 }
 
 // mu += scale sigmoid(-k (o - t)) Sigma eta
@@ -215,37 +280,37 @@ hipError_t launch_mcmc_relocate(Ctx* c, const gs_gaussian_adam* state, int N, in
                                 const float* u, float t_dead, int32_t* src, int32_t* n_moved,
                                 hipStream_t st) {
     if (N <= 0) return hipSuccess;
-    McState s;
     const int K = (sh_degree + 1) * (sh_degree + 1);
     const int rows[5] = {3, 3, 4, 1, 3 * K};
-    for (int q = 0; q < 5; q++) {
-        s.p[q] = state->params[q];
-        s.m[q] = state->exp_avg[q];
-        s.v[q] = state->exp_avg_sq[q];
-        s.rows[q] = rows[q];
-    }
-    s.N = N;
-    // workspace in the record buffer: cdf (8 B per item), counts (4 B), block
-    // sums; the caller's src array, or one in the workspace
-    char* base = reinterpret_cast<char*>(c->rec);
-    uint64_t* cdf = reinterpret_cast<uint64_t*>(base);
-    uint32_t* count = reinterpret_cast<uint32_t*>(base + 8 * (size_t)N);
-    int32_t* srcw = reinterpret_cast<int32_t*>(base + 12 * (size_t)N);
-    uint64_t* bsum = reinterpret_cast<uint64_t*>(base + 16 * (size_t)((N + 1) / 2 * 2));
-    if (!src) src = srcw;
+    Rows<kMaxRows> par = {};
+    Rows<2 * kMaxRows> mom = {};
+    for (int q = 0; q < 5; q++)
+        for (int r = 0; r < rows[q]; r++) {
+            par.p[par.n++] = state->params[q] + (int64_t)r * N;
+            mom.p[mom.n++] = state->exp_avg[q] + (int64_t)r * N;
+            mom.p[mom.n++] = state->exp_avg_sq[q] + (int64_t)r * N;
+        }
+    // workspace in the record buffer (48 B per item, at least 128): prefixes and
+    // the list of the dead (8 B per item each), counts and sources (4 B each; the
+    // caller's src array, if given), the moved words, block sums
     const int nb = (N + kBlock - 1) / kBlock;
-    if (n_moved) {
-        hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t*>(n_moved), 0u, 1, st);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k_mc_weights, dim3(nb), dim3(kBlock), 0, st, s.p[3], N, t_dead, cdf, bsum);
-    hipLaunchKernelGGL(k_mc_block_offsets, dim3(1), dim3(kBlock), 0, st, bsum, nb);
-    hipLaunchKernelGGL(k_mc_cdf, dim3(nb), dim3(kBlock), 0, st, cdf, N, bsum, count);
-    hipLaunchKernelGGL(k_mc_draw, dim3(nb), dim3(kBlock), 0, st, s.p[3], N, t_dead, u, cdf, bsum + nb, src,
-                       count, n_moved);
+    const size_t nw = ((size_t)N + kWave - 1) / kWave;
+    uint64_t* cdf = reinterpret_cast<uint64_t*>(c->rec);
+    int2* list = reinterpret_cast<int2*>(cdf + N);
+    uint64_t* moved = reinterpret_cast<uint64_t*>(list + N);
+    uint64_t* bsum = moved + nw;
+    uint64_t* bdead = bsum + nb + 1;
+    uint32_t* count = reinterpret_cast<uint32_t*>(bdead + nb + 1);
+    if (!src) src = reinterpret_cast<int32_t*>(count + N);
+    const dim3 gb(nb), tb(kBlock);
+    hipLaunchKernelGGL(k_mc_weights, gb, tb, 0, st, par.p[10], N, t_dead, cdf, bsum, bdead, count);
+    hipLaunchKernelGGL(k_mc_block_offsets, dim3(1), tb, 0, st, bsum, bdead, nb, n_moved);
+    hipLaunchKernelGGL(k_mc_draw, gb, tb, 0, st, par.p[10], N, t_dead, u, cdf, bsum, bdead, nb, src, count,
+                       list);
+    hipLaunchKernelGGL(k_mc_sources, gb, tb, 0, st, par.p[10], par.p[3], N, count, src, moved);
     const unsigned g = (unsigned)((N + 255) / 256);
-    hipLaunchKernelGGL(k_mc_sources, dim3(g), dim3(256), 0, st, s, count);
-    hipLaunchKernelGGL(k_mc_copy, dim3(g), dim3(256), 0, st, s, src);
+    hipLaunchKernelGGL(k_mc_copy, dim3(std::min(g, 2048u), par.n), dim3(256), 0, st, par, list, bdead + nb);
+    hipLaunchKernelGGL(k_mc_zero, dim3(g, mom.n), dim3(256), 0, st, mom, N, moved);
     return hipGetLastError();
 }
 
