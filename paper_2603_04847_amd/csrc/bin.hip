@@ -56,13 +56,17 @@ struct WaveUnits {
 };
 
 __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t x, uint32_t& total) {
-    const int lane = __lane_id();
+    // shifts by 1, 2, 4 and 8 inside the rows of 16 lanes, then the carries from
+    // the end of row 0 into row 1, of row 2 into row 3, and of lane 31 into rows
+    // 2 and 3
     uint32_t inc = x;
-    for (int off = 1; off < kWave; off <<= 1) {
-        const uint32_t t = __shfl_up(inc, off, kWave);
-        if (lane >= off) inc += t;
-    }
-    total = __shfl(inc, kWave - 1, kWave);
+    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x111, 0xF, 0xF, false);
+    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x112, 0xF, 0xF, false);
+    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x114, 0xF, 0xF, false);
+    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x118, 0xF, 0xF, false);
+    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x142, 0xA, 0xF, false);
+    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x143, 0xC, 0xF, false);
+    total = (uint32_t)bcast((int)inc, kWave - 1);
     return inc - x;
 }
 
@@ -130,13 +134,13 @@ __device__ __forceinline__ void unit_runs4(const BlockUnit& u, int c, uint32_t (
 #pragma unroll
     for (int i = 0; i < kBlockQuads; i++) {
         const int a = max(u.c0[i] - base, 0), b = min(u.c1[i] - base, 31);
-        S[i] = (u.c0[i] <= u.c1[i] && a <= b) ? ((2u << (b - a)) - 1u) << a : 0u;
+        S[i] = a <= b ? (2u << b) - (1u << a) : 0u;  // (a row without columns: a > 31)
     }
 }
 
 // The mask of block column c + k from the runs: byte k of runs 0-7 gathered with
 // byte permutes (v_perm_b32 selector values 0-3 take bytes of its second
-// operand, 4-7 of its first, 12 gives zero); equal to block_unit_mask.
+// operand, 4-7 of its first, 12 gives zero).
 __device__ __forceinline__ uint64_t runs_mask4(const uint32_t (&S)[kBlockQuads], int k) {
     const uint32_t sa = 0x0C0C0400u + 0x0101u * (uint32_t)k;      // bytes 0, 1
     const uint32_t sb = 0x04000C0Cu + 0x01010000u * (uint32_t)k;  // bytes 2, 3
@@ -145,14 +149,27 @@ __device__ __forceinline__ uint64_t runs_mask4(const uint32_t (&S)[kBlockQuads],
     return ((uint64_t)hi << 32) | lo;
 }
 
+// A word stored at a byte offset: one 32-bit offset serves the four entry arrays
+// (at most 2^30 words each).
+__device__ __forceinline__ void store_at(uint32_t* p, uint32_t at, uint32_t v) {
+    *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(p) + at) = v;
+}
+
 // One (block key; pair, mask) entry per block met, pairs in depth order: rank
 // r's entries fill [off[r], off[r + 1]) (the last rank ends at the total).  The
 // 64 ranks of a wave own one contiguous output range; in each round every lane
 // takes one unit (block row) and writes its entries at the unit's place in the
-// wave's range.  Counts come from adjacent offsets, so the only access by pair
-// index is the record.  Also reports the number of visible pairs (their depth
+// wave's range, one for each block column from its first to its last (an
+// ellipse's rows leave no column between them out; one that rounding did would
+// get a sentinel).  Counts come from adjacent offsets, so the only access by pair
+// index is the record.  VALU-bound (53 of 64 lanes active, about 900 instructions
+// a round of 64 units): 4 x 1600x1066, 63M entries 1093 -> 898 us, 8 uneven
+// views 996 -> 863, 4 x 1237x822 214 -> 180 with the rows' spans branch-free and
+// their bands stepped in float, entries counted by their end columns instead of
+// a bit per column, scans by DPP and one offset for the four stores.  Also
+// reports the number of visible pairs (their depth
 // keys sort before the culled ones' 0xFFFFFFFF).
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) void k_emit(const float4* __restrict__ rec, int N, ViewTable vt,
+__global__ __launch_bounds__(kBlock) void k_emit(const float4* __restrict__ rec, int N, ViewTable vt,
                                                  RasterParams rp, const uint32_t* __restrict__ order,
                                                  uint32_t pmask, const uint32_t* __restrict__ off,
                                                  const uint32_t* __restrict__ keys, int64_t n,
@@ -202,6 +219,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
     s_pair[w][lane] = pair;
     __syncthreads();
     uint32_t done = 0;  // entries of the wave written so far
+    // its slots below the capacity (the last wave's end at lim)
+    const uint32_t room = base < lim ? min(wave_total, lim - base) : 0u;
+    const uint32_t sentinel = (uint32_t)vt.block_off[vt.V];
     bool bound_broken = false;
     for (uint32_t ub = 0; ub < U; ub += kWave) {
         const uint32_t j = ub + lane;
@@ -215,7 +235,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
             const int vq = wu.v[q];
             br = wu.sp[q].r0 / kBlockQuads + (int)(j - wu.upre[q]);
             u = block_unit(wu.sp[q], br, vt.W[vq], vt.H[vq], qg);
-            ne = (uint32_t)block_unit_count(u);
+            ne = (uint32_t)max(u.bc1 - u.bc0 + 1, 0);
         }
         uint32_t rt;
         uint32_t o = done + wave_excl_scan(ne, rt);
@@ -224,12 +244,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
             const uint32_t brow = (uint32_t)vt.block_off[vq] + (uint32_t)(br * vt.bx[vq]);
             const uint32_t pq = s_pair[w][q];
             auto put = [&](int bc, uint64_t m) {
-                if (m == 0) return;
-                if (o < wave_total && base + o < lim) {  // never outside the wave's slots
-                    okey[base + o] = brow + (uint32_t)bc;
-                    opair[base + o] = pq;
-                    omlo[base + o] = (uint32_t)m;
-                    omhi[base + o] = (uint32_t)(m >> 32);
+                if (o < room) {  // never outside the wave's slots
+                    const uint32_t at = 4u * (base + o);
+                    store_at(okey, at, m ? brow + (uint32_t)bc : sentinel);
+                    store_at(opair, at, pq);
+                    store_at(omlo, at, (uint32_t)m);
+                    store_at(omhi, at, (uint32_t)(m >> 32));
                 } else {
                     bound_broken = true;
                 }
@@ -248,11 +268,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) voi
     }
     // slots the count's bound left over get a sentinel block id past every
     // block and no mask, so no list ever reads them
-    for (uint32_t o = done + lane; o < wave_total && base + o < lim; o += kWave) {
-        okey[base + o] = (uint32_t)vt.block_off[vt.V];
-        opair[base + o] = s_pair[w][0];
-        omlo[base + o] = 0;
-        omhi[base + o] = 0;
+    for (uint32_t o = done + lane; o < room; o += kWave) {
+        const uint32_t at = 4u * (base + o);
+        store_at(okey, at, sentinel);
+        store_at(opair, at, s_pair[w][0]);
+        store_at(omlo, at, 0u);
+        store_at(omhi, at, 0u);
     }
     // the bound must hold; if it ever did not, entries were dropped: say so
     if (bound_broken) atomicOr(&diag[kDiagFlags], (uint32_t)GS_FLAG_COUNT_BOUND);

@@ -249,26 +249,33 @@ __device__ __forceinline__ SplatSpan splat_span(const float4& a, const float4& b
     return s;
 }
 
-// Quadrant columns [c0, c1] of quadrant row r met by the splat (c0 > c1:
-// none); ncols = quadrant columns of the view.
-__device__ __forceinline__ void span_cols(const SplatSpan& s, int r, int W, int H, const QuadGrid& g,
-                                          int ncols, int& c0, int& c1) {
+// Quadrant columns [c0, c1] met by the splat in the band of pixel-centre rows
+// ya .. yb (none: c0 > c1); wmax = W - 0.5, last = the view's last quadrant
+// column.  Without branches: a wave's lanes hold unlike splats, and nearly every
+// row slot is in use by some lane.
+constexpr int kNoCols = 1 << 20;  // c0 of a row that meets nothing (its c1: -1)
+
+__device__ __forceinline__ void span_cols(const SplatSpan& s, bool in, float ya, float yb, float wmax,
+                                          int last, const QuadGrid& g, int& c0, int& c1) {
 #pragma clang fp contract(off)
-    c0 = 1;
-    c1 = 0;
-    const float ya = r * g.hh + 0.5f, yb = (float)min(r * g.hh + g.hh, H) - 0.5f;
     float la = fmaxf(ya - s.my, -s.ey), lb = fminf(yb - s.my, s.ey);
-    if (la > lb + kSpanEps) return;
-    if (la > lb) la = lb = 0.5f * (la + lb);
+    in = in && !(la > lb + kSpanEps);
+    const float mid = 0.5f * (la + lb);
+    const bool cross = la > lb;
+    la = cross ? mid : la;
+    lb = cross ? mid : lb;
     // x offsets of the ellipse boundary at height dy: (-B dy -/+ sqrt(2 A t - det dy^2)) / A
     const float dl = fminf(fmaxf(s.dyL, la), lb), dr = fminf(fmaxf(-s.dyL, la), lb);
     const float ql = __builtin_amdgcn_sqrtf(fmaxf(s.t2A - s.det * dl * dl, 0.f));
     const float qr = __builtin_amdgcn_sqrtf(fmaxf(s.t2A - s.det * dr * dr, 0.f));
     const float xl = s.mx + (-s.B * dl - ql) * s.iA - kSpanEps;
     const float xr = s.mx + (-s.B * dr + qr) * s.iA + kSpanEps;
-    if (!(xl <= (float)W - 0.5f) || !(xr >= 0.5f)) return;
+    in = in && xl <= wmax && xr >= 0.5f;
     c0 = max((int)ceilf((xl + 0.5f) * g.ihw - 1.f), 0);
-    c1 = min((int)floorf((xr - 0.5f) * g.ihw), ncols - 1);
+    c1 = min((int)floorf((xr - 0.5f) * g.ihw), last);
+    in = in && c0 <= c1;
+    c0 = in ? c0 : kNoCols;
+    c1 = in ? c1 : -1;
 }
 
 // One Adam step of one element (Algorithm 1 update step): bias-corrected
@@ -327,6 +334,7 @@ constexpr uint32_t kPairMask = (1u << kPairBits) - 1u;
 // non-zero mask on the tile's four quadrants.
 constexpr int kBlockTiles = 4;                  // tiles per block side
 constexpr int kBlockQuads = 2 * kBlockTiles;    // quadrants per block side
+constexpr int kBlockShift = 3;                  // log2 of it
 
 // The four quadrant bits (qx + 2 qy) of tile (sx, sy) of a block in a block mask.
 __device__ __forceinline__ uint32_t tile_bits(uint64_t m, int sx, int sy) {
@@ -344,61 +352,23 @@ struct BlockUnit {
 __device__ __forceinline__ BlockUnit block_unit(const SplatSpan& s, int br, int W, int H,
                                                 const QuadGrid& g) {
     BlockUnit u;
-    const int ncols = (W + g.hw - 1) / g.hw;
-    u.bc0 = 1 << 30;
-    u.bc1 = -1;
+    const int last = (W + g.hw - 1) / g.hw - 1;
+    const float wmax = (float)W - 0.5f, hmax = (float)H - 0.5f;
+    // the rows' bands, exact in float (whole numbers and halves)
+    const float y0 = (float)(kBlockQuads * br * g.hh) + 0.5f;
+    int c0 = kNoCols, c1 = -1;
 #pragma unroll
     for (int i = 0; i < kBlockQuads; i++) {
         const int r = kBlockQuads * br + i;
-        u.c0[i] = 1;
-        u.c1[i] = 0;
+        const float ya = y0 + (float)(i * g.hh), yb = fminf(ya + (float)(g.hh - 1), hmax);
         // r <= s.r1 keeps r inside the view's quadrant rows
-        if (r >= s.r0 && r <= s.r1) span_cols(s, r, W, H, g, ncols, u.c0[i], u.c1[i]);
-        if (u.c0[i] <= u.c1[i]) {
-            u.bc0 = min(u.bc0, u.c0[i] / kBlockQuads);
-            u.bc1 = max(u.bc1, u.c1[i] / kBlockQuads);
-        }
+        span_cols(s, r >= s.r0 && r <= s.r1, ya, yb, wmax, last, g, u.c0[i], u.c1[i]);
+        c0 = min(c0, u.c0[i]);
+        c1 = max(c1, u.c1[i]);
     }
+    u.bc0 = c0 >> kBlockShift;  // (a unit that meets nothing: bc0 > bc1)
+    u.bc1 = c1 >> kBlockShift;
     return u;
-}
-
-// The block mask of unit u in block column bc (0: the splat misses the block).
-// Row i's byte is the run of quadrant columns [c0 - q0, c1 - q0] clipped to
-// [0, 7], built without branches: (0xFF << lo) & (0xFF >> (7 - hi)) with lo
-// clamped to [0, 8] and hi to [-1, 7] is empty whenever lo > hi.
-__device__ __forceinline__ uint64_t block_unit_mask(const BlockUnit& u, int bc) {
-    const int q0 = kBlockQuads * bc;
-    uint32_t lo32 = 0, hi32 = 0;
-#pragma unroll
-    for (int i = 0; i < kBlockQuads; i++) {
-        const int lo = min(max(u.c0[i] - q0, 0), 8);
-        const int hi = min(max(u.c1[i] - q0, -1), 7);
-        const uint32_t byte = (0xFFu << lo) & (0xFFu >> (7 - hi));
-        if (i < 4) lo32 |= byte << (8 * i);
-        else hi32 |= byte << (8 * (i - 4));
-    }
-    return ((uint64_t)hi32 << 32) | lo32;
-}
-
-// Entries of a unit: block columns met by some row (a row meets the block
-// columns c0/8 .. c1/8), counted on a bitmask of the columns from bc0 while
-// they fit in 64 bits, one column at a time beyond.
-__device__ __forceinline__ int block_unit_count(const BlockUnit& u) {
-    if (u.bc0 > u.bc1) return 0;
-    if (u.bc1 - u.bc0 < 64) {
-        uint64_t cols = 0;
-#pragma unroll
-        for (int i = 0; i < kBlockQuads; i++) {
-            if (u.c0[i] > u.c1[i]) continue;
-            const int a = u.c0[i] / kBlockQuads - u.bc0, b = u.c1[i] / kBlockQuads - u.bc0;
-            const uint64_t hi = b >= 63 ? ~0ull : (2ull << b) - 1ull;
-            cols |= hi & ~((1ull << a) - 1ull);
-        }
-        return __popcll(cols);
-    }
-    int n = 0;
-    for (int bc = u.bc0; bc <= u.bc1; bc++) n += block_unit_mask(u, bc) != 0;
-    return n;
 }
 
 // Upper bound of a unit's entries, for sizing only: the block columns met by
@@ -428,7 +398,7 @@ __device__ __forceinline__ int unit_band_count(const SplatSpan& s, int br, int W
     const int ncols = (W + g.hw - 1) / g.hw;
     const int c0 = max((int)ceilf((xl + 0.5f) * g.ihw - 1.f), 0);
     const int c1 = min((int)floorf((xr - 0.5f) * g.ihw), ncols - 1);
-    return c0 <= c1 ? c1 / kBlockQuads - c0 / kBlockQuads + 1 : 0;
+    return c0 <= c1 ? (c1 >> kBlockShift) - (c0 >> kBlockShift) + 1 : 0;
 }
 
 // ------------------------------------------------------------------ host launchers
