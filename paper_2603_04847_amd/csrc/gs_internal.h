@@ -557,7 +557,9 @@ hipError_t launch_pose_compose_bwd(int V, const float* twist, const float* g, fl
 hipError_t launch_adam(const gs_adam_group* groups, int n, int step, const int32_t* step_dev,
                        float b1, float b2, float eps, hipStream_t st);
 hipError_t launch_step_advance(int32_t* step_dev, hipStream_t st);
-hipError_t launch_flush_acc(double* acc, float* out, int n, hipStream_t st);
+// out[i] += acc[i], acc cleared (i < n; none if out is null), and the same of one more value
+hipError_t launch_flush_acc(double* acc, float* out, int n, hipStream_t st, double* acc1 = nullptr,
+                            float* out1 = nullptr);
 // out[6 * rows[v] + e] += acc[6 * v + e]; acc cleared (twists of a sampled batch)
 hipError_t launch_flush_twist_rows(double* acc, float* out, const ViewTable& vt, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t st);

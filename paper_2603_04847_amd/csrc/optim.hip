@@ -143,11 +143,14 @@ __global__ void k_step_advance(int32_t* __restrict__ step_dev) {
     if (threadIdx.x == 0) *step_dev += 1;
 }
 
-__global__ void k_flush_acc(double* __restrict__ acc, float* __restrict__ out, int n) {
+// out[i] += acc[i], i < n; then the one value out1 += acc1 (n1 = 1)
+__global__ void k_flush_acc(double* __restrict__ acc, float* __restrict__ out, int n,
+                            double* __restrict__ acc1, float* __restrict__ out1, int n1) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) {
-        out[i] += (float)acc[i];
-        acc[i] = 0.0;
+    if (i < n + n1) {
+        double* a = i < n ? acc + i : acc1;
+        *(i < n ? out + i : out1) += (float)*a;
+        *a = 0.0;
     }
 }
 
@@ -210,9 +213,11 @@ hipError_t launch_step_advance(int32_t* step_dev, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_flush_acc(double* acc, float* out, int n, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_flush_acc, dim3((n + 255) / 256), dim3(256), 0, st, acc, out, n);
+hipError_t launch_flush_acc(double* acc, float* out, int n, hipStream_t st, double* acc1, float* out1) {
+    const int n1 = out1 ? 1 : 0;
+    n = out ? std::max(n, 0) : 0;
+    if (n + n1 <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_flush_acc, dim3((n + n1 + 255) / 256), dim3(256), 0, st, acc, out, n, acc1, out1, n1);
     return hipGetLastError();
 }
 

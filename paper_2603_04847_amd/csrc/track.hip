@@ -8,8 +8,13 @@
 // words few.  A step whose lanes straddle a camera boundary uses per-lane
 // atomics.  Track-point gradients are
 // scattered with three float atomics per observation (points are spread, so
-// these rarely collide), or, given a point-major index of the observations,
-// summed per point by a kernel of their own with no atomics.
+// these rarely collide), which bound this form: the memory takes an atomic
+// instruction one address line after another, so the wave first turns its 64
+// gradients through LDS and a point's three words go out from adjacent lanes,
+// one line instead of one in each of three instructions (430k observations of
+// 150 cameras: 94.6 -> 53 us; 4.3M of 1000: 736 -> 348).  Or, given a
+// point-major index of the observations, they are summed per point by a
+// kernel of their own with no atomics.
 //
 // Given also the observations' cameras and pixels copied into point-major
 // order (once per scene), the whole term is one pass over the points that
@@ -93,7 +98,9 @@ __global__ __launch_bounds__(kBlock) void k_track(
     double* __restrict__ loss_acc, uint32_t* __restrict__ diag) {
     __shared__ float s_loss[kBlock / kWave];
     __shared__ uint32_t s_mask[kBlock / kWave];
-    const int lane = __lane_id();
+    __shared__ float s_vx[kBlock / kWave][3 * kWave];
+    __shared__ int s_k[kBlock / kWave][kWave];
+    const int lane = __lane_id(), wave = threadIdx.x / kWave;
     float lo_sum = 0.f;
     uint32_t n_masked = 0;
     // this workgroup's range, a multiple of the workgroup size long
@@ -146,7 +153,7 @@ __global__ __launch_bounds__(kBlock) void k_track(
             if (v_X) {
 #pragma unroll
                 for (int c = 0; c < 3; c++)
-                    atomicAdd(v_X + 3 * (int64_t)k + c, R[c] * vp[0] + R[3 + c] * vp[1] + R[6 + c] * vp[2]);
+                    s_vx[wave][3 * lane + c] = R[c] * vp[0] + R[3 + c] * vp[1] + R[6 + c] * vp[2];
             }
             tw[0] = vp[0];
             tw[1] = vp[1];
@@ -183,6 +190,18 @@ __global__ __launch_bounds__(kBlock) void k_track(
     }
     // twist: one camera for the whole wave is the common case
     const uint64_t live = __ballot(ok_idx && !masked);
+    // the points' gradients, turned so that a point's three words are adjacent
+    // lanes' and reach the memory as one request
+    if (v_X && live != 0) {
+        s_k[wave][lane] = k;
+        wave_lds_sync();
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            const int e = i * kWave + lane, q = e / 3;
+            if (live >> q & 1) atomicAdd(v_X + 3 * (int64_t)s_k[wave][q] + e % 3, s_vx[wave][e]);
+        }
+        wave_lds_sync();
+    }
     if (live != 0) {
         const int first = __builtin_ctzll(live);
         const int c0 = bcast(ci, first);
@@ -473,11 +492,7 @@ hipError_t launch_track_scratch(const TrackScratch& sc, const float* X, int Pt, 
             return hipGetLastError();
         }
     }
-    hipError_t e = hipSuccess;
-    if (v_twist && (e = launch_flush_acc(sc.twist_acc, v_twist, 6 * n_cams, st)) != hipSuccess)
-        return e;
-    if (loss) return launch_flush_acc(sc.loss_acc, loss, 1, st);
-    return hipSuccess;
+    return launch_flush_acc(sc.twist_acc, v_twist, 6 * n_cams, st, sc.loss_acc, loss);
 }
 
 hipError_t launch_track_index(Ctx* c, const int32_t* obs_pt, int M, int Pt, int32_t* pt_off,
