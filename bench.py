@@ -695,7 +695,7 @@ CALL_KERNELS = {
     "raster_bwd": lambda k: k.startswith("k_render_bwd<"),
     "photo": lambda k: k == "k_photo",
     "project_bwd_adam": lambda k: k in ("k_project_bwd_color<3, true>", "k_project_bwd_geom<true>"),
-    "track": lambda k: k in ("k_track", "k_track_points", "k_track_pm", "k_track_pm_reduce"),
+    "track": lambda k: k.split("<")[0] in ("k_track", "k_track_points", "k_track_pm", "k_track_pm_reduce"),
     "adam": lambda k: k == "k_adam",
 }
 

@@ -305,25 +305,6 @@ __global__ __launch_bounds__(kWave) void k_ba_windows(int Pt, const int32_t* __r
     }
 }
 
-template <int CTRL, int ROW_MASK = 0xf>
-__device__ __forceinline__ double dpp_f64(double x) {
-    const uint64_t b = __double_as_longlong(x);
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROW_MASK, 0xf, true);
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROW_MASK, 0xf, true);
-    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
-}
-
-// one step of the segmented sums below
-template <int CTRL, int N>
-__device__ __forceinline__ void seg_step(double (&t)[N], bool add) {
-    double y[N];
-#pragma unroll
-    for (int i = 0; i < N; i++) y[i] = dpp_f64<CTRL>(t[i]);
-    if (add)
-#pragma unroll
-        for (int i = 0; i < N; i++) t[i] += y[i];
-}
-
 // The segment (point) a lane of a window of `cnt` observations belongs to: its
 // first and last lane.
 struct Segment {
@@ -335,21 +316,6 @@ __device__ __forceinline__ Segment segment_of(uint64_t heads, int cnt, int lane)
     const uint64_t above = heads & ~upto;
     return Segment{63 - __clzll((long long)(heads & upto)),
                    above ? __ffsll((unsigned long long)above) - 2 : cnt - 1};
-}
-
-// t summed over the lanes of each segment, whole at the segment's last lane.
-// Shifts by 1, 2, 4 and 8 inside the rows of 16 lanes, then the carries from
-// the end of row 0 into row 1, of row 2 into row 3, and of lane 31 into rows 2
-// and 3.
-template <int N>
-__device__ __forceinline__ void seg_sum(double (&t)[N], int lane, int head) {
-    const int r = lane & 15, d = lane - head;
-    seg_step<0x111>(t, d >= 1 && r >= 1);
-    seg_step<0x112>(t, d >= 2 && r >= 2);
-    seg_step<0x114>(t, d >= 4 && r >= 4);
-    seg_step<0x118>(t, d >= 8 && r >= 8);
-    seg_step<0x142>(t, d > r && (lane & 16));
-    seg_step<0x143>(t, head < 32 && lane >= 32);
 }
 
 // the index of lane's point in a window

@@ -156,6 +156,49 @@ __device__ __forceinline__ int wave_max_i(int v) {
     return v;
 }
 
+template <int CTRL, int ROW_MASK = 0xf>
+__device__ __forceinline__ double dpp_f64(double x) {
+    const uint64_t b = __double_as_longlong(x);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROW_MASK, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROW_MASK, 0xf, true);
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_any(double x) {
+    return dpp_f64<CTRL>(x);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_any(float x) {
+    return dpp_f<CTRL>(x);
+}
+
+// one step of the segmented sums below
+template <int CTRL, int N, typename T>
+__device__ __forceinline__ void seg_step(T (&t)[N], bool add) {
+    T y[N];
+#pragma unroll
+    for (int i = 0; i < N; i++) y[i] = dpp_any<CTRL>(t[i]);
+    if (add)
+#pragma unroll
+        for (int i = 0; i < N; i++) t[i] += y[i];
+}
+
+// t summed over the lanes of each segment, whole at the segment's last lane.
+// Shifts by 1, 2, 4 and 8 inside the rows of 16 lanes, then the carries from
+// the end of row 0 into row 1, of row 2 into row 3, and of lane 31 into rows 2
+// and 3.
+template <int N, typename T>
+__device__ __forceinline__ void seg_sum(T (&t)[N], int lane, int head) {
+    const int r = lane & 15, d = lane - head;
+    seg_step<0x111>(t, d >= 1 && r >= 1);
+    seg_step<0x112>(t, d >= 2 && r >= 2);
+    seg_step<0x114>(t, d >= 4 && r >= 4);
+    seg_step<0x118>(t, d >= 8 && r >= 8);
+    seg_step<0x142>(t, d > r && (lane & 16));
+    seg_step<0x143>(t, head < 32 && lane >= 32);
+}
+
 // Orders one wave's own LDS accesses (its stores before its later loads) with
 // no workgroup barrier, which would also wait for the loads in flight.
 __device__ __forceinline__ void wave_lds_sync() {
@@ -518,7 +561,7 @@ hipError_t launch_photo(Ctx* c, const ViewTable& vt, const float* rgb, const flo
 
 // track.hip
 // Workgroups of the point-major track pass (each keeps its twist sums in LDS).
-constexpr int kTrackPmBlocks = 512;
+constexpr int kTrackPmBlocks = 256;
 hipError_t launch_track(Ctx* c, const float* X, int Pt, const float* viewmat, const float* intr,
                         int n_cams, const int32_t* obs_cam, const int32_t* obs_pt,
                         const float* obs_xy, int M, float delta, float lambda, float near_plane,

@@ -19,7 +19,7 @@
 // Given also the observations' cameras and pixels copied into point-major
 // order (once per scene), the whole term is one pass over the points that
 // reads every array in order: each workgroup keeps per-camera twist sums in
-// LDS (float atomics there, no global atomics), writes them out once, and a
+// LDS (double atomics there, no global atomics), writes them out once, and a
 // second kernel sums the workgroups' rows in a fixed order in double.  Without the copies the
 // camera-major pass gathers a random point per observation and the point
 // pass a random observation per index entry.
@@ -45,20 +45,17 @@ struct ObsTerms {
     bool masked;
 };
 
-__device__ __forceinline__ void obs_terms(const float* __restrict__ X, int k,
-                                          const float* __restrict__ viewmat,
-                                          const float* __restrict__ intr, int ci,
-                                          const float* __restrict__ obs_xy, int o, float delta,
-                                          float lambda, float near_plane, ObsTerms& T) {
+// C: the camera's [R | t] rows (12 floats), then fx, fy, cx, cy
+__device__ __forceinline__ void obs_terms(const float (&C)[16], const float (&Xk)[3], float px, float py,
+                                          float delta, float lambda, float near_plane, ObsTerms& T) {
     float t[3];
 #pragma unroll
     for (int r = 0; r < 3; r++) {
 #pragma unroll
-        for (int c = 0; c < 3; c++) T.R[3 * r + c] = viewmat[12 * ci + 4 * r + c];
-        t[r] = viewmat[12 * ci + 4 * r + 3];
+        for (int c = 0; c < 3; c++) T.R[3 * r + c] = C[4 * r + c];
+        t[r] = C[4 * r + 3];
     }
-    const float fx = intr[4 * ci], fy = intr[4 * ci + 1], cx = intr[4 * ci + 2], cy = intr[4 * ci + 3];
-    const float Xk[3] = {X[3 * (int64_t)k], X[3 * (int64_t)k + 1], X[3 * (int64_t)k + 2]};
+    const float fx = C[12], fy = C[13], cx = C[14], cy = C[15];
 #pragma unroll
     for (int r = 0; r < 3; r++)
         T.p[r] = T.R[3 * r] * Xk[0] + T.R[3 * r + 1] * Xk[1] + T.R[3 * r + 2] * Xk[2] + t[r];
@@ -66,8 +63,8 @@ __device__ __forceinline__ void obs_terms(const float* __restrict__ X, int k,
     if (T.masked) return;
     const float iz = 1.f / T.p[2];
     const float u = T.p[0] * iz, w = T.p[1] * iz;
-    T.r0 = fx * u + cx - obs_xy[2 * (int64_t)o];
-    T.r1 = fy * w + cy - obs_xy[2 * (int64_t)o + 1];
+    T.r0 = fx * u + cx - px;
+    T.r1 = fy * w + cy - py;
     const float s = T.r0 * T.r0 + T.r1 * T.r1;
     float drho;
     if (s <= delta * delta) {
@@ -87,6 +84,26 @@ __device__ __forceinline__ void obs_terms(const float* __restrict__ X, int k,
     T.vp[0] = T.j00 * g0;
     T.vp[1] = T.j11 * g1;
     T.vp[2] = T.j02 * g0 + T.j12 * g1;
+}
+
+__device__ __forceinline__ void load_camera(const float* __restrict__ viewmat,
+                                            const float* __restrict__ intr, int ci, float (&C)[16]) {
+#pragma unroll
+    for (int e = 0; e < 12; e++) C[e] = viewmat[12 * ci + e];
+#pragma unroll
+    for (int e = 0; e < 4; e++) C[12 + e] = intr[4 * ci + e];
+}
+
+// the terms of observation o, point k and camera ci read from memory
+__device__ __forceinline__ void obs_terms(const float* __restrict__ X, int k,
+                                          const float* __restrict__ viewmat,
+                                          const float* __restrict__ intr, int ci,
+                                          const float* __restrict__ obs_xy, int o, float delta,
+                                          float lambda, float near_plane, ObsTerms& T) {
+    float C[16];
+    load_camera(viewmat, intr, ci, C);
+    const float Xk[3] = {X[3 * (int64_t)k], X[3 * (int64_t)k + 1], X[3 * (int64_t)k + 2]};
+    obs_terms(C, Xk, obs_xy[2 * (int64_t)o], obs_xy[2 * (int64_t)o + 1], delta, lambda, near_plane, T);
 }
 
 __global__ __launch_bounds__(kBlock) void k_track(
@@ -282,70 +299,146 @@ __global__ __launch_bounds__(kBlock) void k_track_points(
     for (int c = 0; c < 3; c++) v_X[3 * (int64_t)k + c] += acc[c];
 }
 
-// The point-major pass (see the file comment): one thread per point (grid
-// stride), its observations' terms from the point-major copies; v_X written
-// once per point; twist sums per workgroup in LDS, 6 n_cams floats.  (One
-// thread per observation, the point found by a search of the chunk's offsets
-// in LDS and its gradient gathered by LDS atomics, measured 30% slower: the
-// search is a chain of dependent LDS loads and a point's observations collide
-// on its three words.)
-__global__ __launch_bounds__(kBlock) void k_track_pm(
+// The point-major pass (see the file comment).  A wave takes 64 points at a
+// time and walks their observations, which lie in one run, 64 by 64: a lane
+// finds its observation's point by marking each point's first lane in LDS and
+// a running maximum, takes the point's position from the point's lane, and
+// the point gradients are summed over the lanes of each point and handed back
+// to the point's lane, which writes v_X once.  So every lane has an
+// observation whatever the tracks' lengths, and every read is in order but the
+// cameras', which are staged in LDS where they fit beside the twist sums.
+// Twist sums: six doubles per camera and workgroup, component by component
+// (random cameras then spread over the banks), by LDS atomics.  What bounds it:
+// the chain of a step (loads, the owner's marks, the camera's row, the six
+// atomics) on the few waves that the LDS leaves room for.  Measured alone,
+// with the sum over the rows, against a thread per point with its sums in one
+// float per component: 6.5M observations of 1000 cameras 279 -> 70 us, 428k of
+// 150 48 -> 18.
+constexpr int kPmThreads = 1024;
+constexpr int kPmCam = 20;         // floats of a staged camera: 16, and a stride that spreads the banks
+constexpr int kPmStagedCams = 1200;  // 48 + 80 B a camera, and under 6 KB besides, in 160 KB
+
+// inclusive running maximum over the lanes, of values >= 0
+__device__ __forceinline__ int wave_run_max(int v) {
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));
+    return max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));
+}
+
+template <bool STAGED>
+__global__ __launch_bounds__(kPmThreads) void k_track_pm(
     const float* __restrict__ X, int Pt, const float* __restrict__ viewmat,
     const float* __restrict__ intr, int n_cams, const int32_t* __restrict__ pt_off,
     const int32_t* __restrict__ pm_cam, const float* __restrict__ pm_xy, float delta, float lambda,
     float near_plane, float* __restrict__ v_X, float* __restrict__ part,
     double* __restrict__ loss_part, uint32_t* __restrict__ diag) {
-    extern __shared__ float s_tw[];  // [n_cams][6]
-    __shared__ float s_loss[kBlock / kWave];
-    __shared__ uint32_t s_mask[kBlock / kWave];
-    for (int q = threadIdx.x; q < 6 * n_cams; q += kBlock) s_tw[q] = 0.f;
+    constexpr int kPmWaves = kPmThreads / kWave;
+    extern __shared__ __attribute__((aligned(16))) double s_tw[];  // [6][n_cams], then the cameras [n_cams][kPmCam] floats
+    __shared__ int s_own[kPmWaves][kWave];
+    __shared__ float s_loss[kPmWaves];
+    __shared__ uint32_t s_mask[kPmWaves];
+    float* s_cam = reinterpret_cast<float*>(s_tw + 6 * n_cams);
+    const int lane = __lane_id(), w = threadIdx.x / kWave;
+    for (int q = threadIdx.x; q < 6 * n_cams; q += kPmThreads) s_tw[q] = 0.0;
+    if (STAGED) {
+        for (int q = threadIdx.x; q < 12 * n_cams; q += kPmThreads) s_cam[q / 12 * kPmCam + q % 12] = viewmat[q];
+        for (int q = threadIdx.x; q < 4 * n_cams; q += kPmThreads) s_cam[q / 4 * kPmCam + 12 + q % 4] = intr[q];
+    }
     __syncthreads();
     float lo_sum = 0.f;
     uint32_t n_masked = 0;
-    for (int k = blockIdx.x * kBlock + threadIdx.x; k < Pt; k += gridDim.x * kBlock) {
-        const int j0 = pt_off[k], j1 = pt_off[k + 1];
-        if (j0 >= j1) continue;
+    const int chunks = (Pt + kWave - 1) / kWave;
+    for (int c = w * gridDim.x + blockIdx.x; c < chunks; c += gridDim.x * kPmWaves) {
+        const int k = c * kWave + lane;
+        // lanes past the last point hold the empty run at its end
+        const int j0 = pt_off[min(k, Pt)], j1 = pt_off[min(k + 1, Pt)];
+        const int kc = min(k, Pt - 1);
+        const float Xl[3] = {X[3 * (int64_t)kc], X[3 * (int64_t)kc + 1], X[3 * (int64_t)kc + 2]};
+        const int end = bcast(j1, kWave - 1);
         float acc[3] = {0.f, 0.f, 0.f};
-        for (int j = j0; j < j1; j++) {
-            const int ci = pm_cam[j];
-            if (ci < 0 || ci >= n_cams) continue;
-            ObsTerms T;
-            obs_terms(X, k, viewmat, intr, ci, pm_xy, j, delta, lambda, near_plane, T);
-            if (T.masked) {
-                n_masked++;
-                continue;
+        for (int base = bcast(j0, 0); base < end; base += kWave) {
+            const int j = base + lane;
+            const bool in = j < end;
+            const int ci = in ? pm_cam[j] : -1;
+            const float px = in ? pm_xy[2 * (int64_t)j] : 0.f, py = in ? pm_xy[2 * (int64_t)j + 1] : 0.f;
+            // this lane's point has observations in the step
+            const bool here = j1 > j0 && j1 > base && j0 < base + kWave;
+            s_own[w][lane] = 0;
+            wave_lds_sync();
+            if (here) s_own[w][max(j0 - base, 0)] = lane;
+            wave_lds_sync();
+            const int mark = s_own[w][lane];
+            const int own = wave_run_max(mark);
+            const uint64_t heads = __ballot(mark != 0) | 1ull;
+            const int head = 63 - __clzll((long long)(heads & (~0ull >> (63 - lane))));
+            float Xk[3];
+#pragma unroll
+            for (int e = 0; e < 3; e++) Xk[e] = __shfl(Xl[e], own, kWave);
+            float g[3] = {0.f, 0.f, 0.f};
+            if (ci >= 0 && ci < n_cams) {
+                float C[16];
+                if (STAGED) {
+                    const float4* row = reinterpret_cast<const float4*>(s_cam + ci * kPmCam);
+#pragma unroll
+                    for (int e = 0; e < 4; e++) {
+                        const float4 q = row[e];
+                        C[4 * e] = q.x;
+                        C[4 * e + 1] = q.y;
+                        C[4 * e + 2] = q.z;
+                        C[4 * e + 3] = q.w;
+                    }
+                } else {
+                    load_camera(viewmat, intr, ci, C);
+                }
+                ObsTerms T;
+                obs_terms(C, Xk, px, py, delta, lambda, near_plane, T);
+                if (T.masked) {
+                    n_masked++;
+                } else {
+                    lo_sum += lambda * T.rho;
+                    const float* R = T.R;
+                    const float* p = T.p;
+                    const float* vp = T.vp;
+#pragma unroll
+                    for (int e = 0; e < 3; e++) g[e] = R[e] * vp[0] + R[3 + e] * vp[1] + R[6 + e] * vp[2];
+                    double* tw = s_tw + ci;
+                    atomicAdd(tw, (double)vp[0]);
+                    atomicAdd(tw + n_cams, (double)vp[1]);
+                    atomicAdd(tw + 2 * n_cams, (double)vp[2]);
+                    atomicAdd(tw + 3 * n_cams, (double)(p[1] * vp[2] - p[2] * vp[1]));
+                    atomicAdd(tw + 4 * n_cams, (double)(p[2] * vp[0] - p[0] * vp[2]));
+                    atomicAdd(tw + 5 * n_cams, (double)(p[0] * vp[1] - p[1] * vp[0]));
+                }
             }
-            lo_sum += lambda * T.rho;
-            const float* R = T.R;
-            const float* p = T.p;
-            const float* vp = T.vp;
+            seg_sum(g, lane, head);
+            const int tail = here ? min(j1 - base, kWave) - 1 : 0;
 #pragma unroll
-            for (int c = 0; c < 3; c++) acc[c] += R[c] * vp[0] + R[3 + c] * vp[1] + R[6 + c] * vp[2];
-            float* tw = s_tw + 6 * ci;
-            atomicAdd(tw + 0, vp[0]);
-            atomicAdd(tw + 1, vp[1]);
-            atomicAdd(tw + 2, vp[2]);
-            atomicAdd(tw + 3, p[1] * vp[2] - p[2] * vp[1]);
-            atomicAdd(tw + 4, p[2] * vp[0] - p[0] * vp[2]);
-            atomicAdd(tw + 5, p[0] * vp[1] - p[1] * vp[0]);
+            for (int e = 0; e < 3; e++) {
+                const float s = __shfl(g[e], tail, kWave);
+                acc[e] += here ? s : 0.f;
+            }
         }
+        if (j1 > j0)
 #pragma unroll
-        for (int c = 0; c < 3; c++) v_X[3 * (int64_t)k + c] += acc[c];
+            for (int e = 0; e < 3; e++) v_X[3 * (int64_t)k + e] += acc[e];
     }
     const float ls = wave_sum(lo_sum);
     uint32_t nm = n_masked;
     for (int off = 32; off > 0; off >>= 1) nm += __shfl_xor(nm, off, kWave);
-    if (__lane_id() == 0) {
-        s_loss[threadIdx.x / kWave] = ls;
-        s_mask[threadIdx.x / kWave] = nm;
+    if (lane == 0) {
+        s_loss[w] = ls;
+        s_mask[w] = nm;
     }
     __syncthreads();
     float* row = part + (int64_t)blockIdx.x * 6 * n_cams;
-    for (int q = threadIdx.x; q < 6 * n_cams; q += kBlock) row[q] = s_tw[q];
+    for (int q = threadIdx.x; q < 6 * n_cams; q += kPmThreads) row[q] = (float)s_tw[q];
     if (threadIdx.x == 0) {
         double tot = 0.0;
         uint32_t tm = 0;
-        for (int q = 0; q < kBlock / kWave; q++) {
+        for (int q = 0; q < kPmWaves; q++) {
             tot += s_loss[q];
             tm += s_mask[q];
         }
@@ -355,38 +448,36 @@ __global__ __launch_bounds__(kBlock) void k_track_pm(
 }
 
 // Sum of the point-major pass's workgroup rows, in double and a fixed order:
-// 64 columns per workgroup, eight waves over interleaved rows; workgroup 0
-// also sums the loss.
-constexpr int kPmReduceWaves = 8;
+// 64 columns per workgroup, sixteen waves over interleaved rows, several loads
+// of each in flight; the last workgroup sums the loss instead.
+constexpr int kPmReduceWaves = 16;
 
 __global__ __launch_bounds__(kWave * kPmReduceWaves) void k_track_pm_reduce(
-    const float* __restrict__ part, const double* __restrict__ loss_part, int nblk, int n6,
+    const float* __restrict__ part, const double* __restrict__ loss_part, int nblk, int n_cams,
     float* __restrict__ v_twist, float* __restrict__ loss) {
     __shared__ double s[kPmReduceWaves][kWave];
     const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
-    const int q = blockIdx.x * kWave + lane;
+    if (blockIdx.x == gridDim.x - 1) {
+        if (w != 0) return;
+        double l = 0.0;
+        for (int b = lane; b < nblk; b += kWave) l += loss_part[b];
+        for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, kWave);
+        if (lane == 0) *loss += (float)l;
+        return;
+    }
+    const int n6 = 6 * n_cams, q = blockIdx.x * kWave + lane;
     double a = 0.0;
-    if (q < n6)
+    if (q < n6) {
+#pragma unroll 8
         for (int b = w; b < nblk; b += kPmReduceWaves) a += part[(int64_t)b * n6 + q];
+    }
     s[w][lane] = a;
     __syncthreads();
     if (w == 0 && q < n6) {
         double t = 0.0;
+#pragma unroll
         for (int i = 0; i < kPmReduceWaves; i++) t += s[i][lane];
-        v_twist[q] += (float)t;
-    }
-    if (blockIdx.x == 0) {
-        __syncthreads();
-        double l = 0.0;
-        for (int b = threadIdx.x; b < nblk; b += kWave * kPmReduceWaves) l += loss_part[b];
-        s[w][lane] = l;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double t = 0.0;
-            for (int i = 0; i < kPmReduceWaves; i++)
-                for (int j = 0; j < kWave; j++) t += s[i][j];
-            *loss += (float)t;
-        }
+        v_twist[6 * (q % n_cams) + q / n_cams] += (float)t;
     }
 }
 
@@ -451,15 +542,26 @@ hipError_t launch_track(Ctx* c, const float* X, int Pt, const float* viewmat, co
     const bool pm = pm_cam && pm_xy && pt_off && pt_obs && v_X && v_twist && loss && !residual &&
                     !J_pose && !J_X && n_cams <= c->pm_cams && c->track_part;
     if (pm && M > 0 && Pt > 0) {
-        hipLaunchKernelGGL(k_track_pm, dim3(kTrackPmBlocks), dim3(kBlock), sizeof(float) * 6 * n_cams, st,
-                           X, Pt, viewmat, intr, n_cams, pt_off, pm_cam, pm_xy, delta, lambda, near_plane,
-                           v_X, c->track_part, c->track_loss_part, c->diag);
+        // four chunks of 64 points a workgroup until every CU has one: fewer
+        // workgroups are fewer rows to sum
+        const int chunks = (Pt + kWave - 1) / kWave;
+        const int nblk = std::min((chunks + 3) / 4, kTrackPmBlocks);
+        const size_t tw = sizeof(double) * 6 * n_cams, cams = sizeof(float) * kPmCam * n_cams;
+        // cameras past what the LDS holds beside their sums are read from
+        // memory (the L2 holds them)
+        if (n_cams <= kPmStagedCams)
+            hipLaunchKernelGGL(k_track_pm<true>, dim3(nblk), dim3(kPmThreads), tw + cams, st, X, Pt, viewmat, intr,
+                               n_cams, pt_off, pm_cam, pm_xy, delta, lambda, near_plane, v_X, c->track_part,
+                               c->track_loss_part, c->diag);
+        else
+            hipLaunchKernelGGL(k_track_pm<false>, dim3(nblk), dim3(kPmThreads), tw, st, X, Pt, viewmat, intr,
+                               n_cams, pt_off, pm_cam, pm_xy, delta, lambda, near_plane, v_X, c->track_part,
+                               c->track_loss_part, c->diag);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        const int n6 = 6 * n_cams;
-        hipLaunchKernelGGL(k_track_pm_reduce, dim3((unsigned)std::max((n6 + kWave - 1) / kWave, 1)),
-                           dim3(kWave * kPmReduceWaves), 0, st, c->track_part, c->track_loss_part,
-                           kTrackPmBlocks, n6, v_twist, loss);
+        hipLaunchKernelGGL(k_track_pm_reduce, dim3((unsigned)((6 * n_cams + kWave - 1) / kWave + 1)),
+                           dim3(kWave * kPmReduceWaves), 0, st, c->track_part, c->track_loss_part, nblk, n_cams,
+                           v_twist, loss);
         return hipGetLastError();
     }
     const TrackScratch sc = {c->twist_track, c->loss_acc + 1, c->diag};
