@@ -498,7 +498,26 @@ __global__ __launch_bounds__(kBlock) void k_tile_ranges(const uint32_t* __restri
 // of q, for the block of the chunk's first entry: tbase of that block plus the
 // chunk prefix (cb[16 c + q]).  Chunks whose entries all lie in that block
 // (nearly all) need nothing else.
+// The block of the sorted entry j from the blocks' ends (which never fall), the
+// first search over all of them, the second upwards from block B; NB past the last.
+__device__ __forceinline__ uint32_t block_of(const int32_t* __restrict__ branges, uint32_t NB, int64_t j) {
+    uint32_t lo = 0, hi = NB;
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi) / 2;
+        if (branges[2 * (int64_t)mid + 1] <= j) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo;
+}
+__device__ __forceinline__ uint32_t block_from(const int32_t* __restrict__ branges, uint32_t NB, int64_t j,
+                                               uint32_t B) {
+    while (B < NB && branges[2 * (int64_t)B + 1] <= j) B++;
+    return B;
+}
+
+// bkey: the sorted entries' block ids, or null and then branges is searched
 __global__ __launch_bounds__(kBlock) void k_chunk_bases(const uint32_t* __restrict__ bkey,
+                                                        const int32_t* __restrict__ branges,
                                                         const uint32_t* __restrict__ used,
                                                         const uint32_t* __restrict__ cpre,
                                                         const uint32_t* __restrict__ tbase,
@@ -510,7 +529,7 @@ __global__ __launch_bounds__(kBlock) void k_chunk_bases(const uint32_t* __restri
     const int64_t c = g / kBlockSub;
     const int q = (int)(g % kBlockSub);
     if (c >= max_chunks || c * kChunk >= n) return;
-    const uint32_t B0 = bkey[c * kChunk];
+    const uint32_t B0 = bkey ? bkey[c * kChunk] : block_of(branges, NB, c * kChunk);
     if (B0 < NB) cb[g] = tbase[(int64_t)B0 * kBlockSub + q] + cpre[(int64_t)q * stride + c];
 }
 
@@ -526,7 +545,7 @@ __global__ __launch_bounds__(kBlock) void k_chunk_bases(const uint32_t* __restri
 constexpr int kStage = 2048;  // staged tile entries per wave
 
 __global__ __launch_bounds__(kBlock) void k_chunk_expand(
-    const uint32_t* __restrict__ bkey, const uint32_t* __restrict__ pairs,
+    const uint32_t* __restrict__ bkey, const int32_t* __restrict__ branges, const uint32_t* __restrict__ pairs,
     const uint32_t* __restrict__ mlo, const uint32_t* __restrict__ mhi,
     const uint32_t* __restrict__ used, const uint32_t* __restrict__ tused,
     const uint32_t* __restrict__ cpre, const uint32_t* __restrict__ tbase,
@@ -544,12 +563,13 @@ __global__ __launch_bounds__(kBlock) void k_chunk_expand(
     for (int64_t c = (int64_t)blockIdx.x * kWaves + w; c * kChunk < n; c += nw) {
         uint64_t m[kChunkSteps];
         uint32_t B[kChunkSteps], pr[kChunkSteps];
+        const uint32_t Bc = bkey ? 0u : block_of(branges, NB, c * kChunk);
 #pragma unroll
         for (int u = 0; u < kChunkSteps; u++) {
             const int64_t j = c * kChunk + u * kWave + lane;
             const int64_t jc = min(j, n - 1);  // unconditional loads, dropped past the end
             const uint64_t mm = ((uint64_t)mhi[jc] << 32) | mlo[jc];
-            B[u] = bkey[jc];
+            B[u] = bkey ? bkey[jc] : block_from(branges, NB, jc, Bc);
             pr[u] = pairs[jc];
             // sentinel entries (unfilled slots) have B = NB and no mask
             m[u] = (j < n && B[u] < NB) ? mm : 0ull;
@@ -736,14 +756,22 @@ hipError_t launch_bin(Ctx* c, const ViewTable& vt, int N, const RasterParams& rp
         // the pair and both mask words travel with the block key
         uint32_t* K[2] = {c->ik[0], c->ik[1]};
         uint32_t* Vv[3][2] = {{c->iv[0], c->iv[1]}, {c->im[0], c->im[1]}, {c->im[0] + I, c->im[1] + I}};
-        const int side2 = radix_sort_kv3(K, Vv, I, used, 0, bbits, c->hist, c->scan_scratch, c->diag + kDiagFlags, st, &e);
+        // one pass where its digit counts pay: see wide_sort_kv3.  Its scratch is
+        // the key buffer it does not write
+        const bool wide = wide_sort_kv3(K[0], Vv, I, used, NB + 1, K[1], I, c->scan_scratch, c->diag + kDiagFlags,
+                                        c->ranges, st, &e);
+        const int side2 = wide ? 1
+                               : radix_sort_kv3(K, Vv, I, used, 0, bbits, c->hist, c->scan_scratch,
+                                                c->diag + kDiagFlags, st, &e);
         if (e != hipSuccess) return e;
         c->block_side = side2;
+        c->block_keyed = !wide;
         const uint32_t* bmlo = c->im[side2];
         const uint32_t* bmhi = c->im[side2] + I;
         const unsigned gi = (unsigned)std::min<int64_t>((I + kBlock - 1) / kBlock, 4096);
-        hipLaunchKernelGGL(k_ranges, dim3(gi), dim3(kBlock), 0, st, c->ik[side2], used, c->ranges,
-                           (uint32_t)NB);
+        if (!wide)
+            hipLaunchKernelGGL(k_ranges, dim3(gi), dim3(kBlock), 0, st, c->ik[side2], used, c->ranges,
+                               (uint32_t)NB);
         // tile lists: chunk counts and their scan, per-block prefixes and tile
         // list lengths, the tile scan and ranges (the entries follow at the end)
         if (T > 0) {
@@ -813,13 +841,14 @@ hipError_t launch_bin(Ctx* c, const ViewTable& vt, int N, const RasterParams& rp
 hipError_t launch_expand_lists(Ctx* c, hipStream_t st) {
     const int64_t NB = c->n_blocks, nch = c->nchunks, I = c->cap.max_isect;
     const int side = c->block_side;
+    const uint32_t* bkey = c->block_keyed ? c->ik[side] : nullptr;
     const uint32_t* used = c->scalars + 1;
     const uint32_t* tused = c->scalars + 3;
     const unsigned gch = (unsigned)std::min<int64_t>((nch + kWaves - 1) / kWaves, 8192);
     hipLaunchKernelGGL(k_chunk_bases, dim3((unsigned)((nch * kBlockSub + kBlock - 1) / kBlock)),
-                       dim3(kBlock), 0, st, c->ik[side], used, c->ccnt, c->tbase, (uint32_t)NB, nch,
+                       dim3(kBlock), 0, st, bkey, c->ranges, used, c->ccnt, c->tbase, (uint32_t)NB, nch,
                        c->cbase);
-    hipLaunchKernelGGL(k_chunk_expand, dim3(gch), dim3(kBlock), 0, st, c->ik[side], c->iv[side],
+    hipLaunchKernelGGL(k_chunk_expand, dim3(gch), dim3(kBlock), 0, st, bkey, c->ranges, c->iv[side],
                        c->im[side], c->im[side] + I, used, tused, c->ccnt, c->tbase, c->cbase,
                        (uint32_t)NB, c->tids);
     c->lists_lazy = false;

@@ -496,6 +496,14 @@ int radix_sort_pairs(uint32_t* ka, uint32_t* va, uint32_t* kb, uint32_t* vb, int
 int radix_sort_kv3(uint32_t* K[2], uint32_t* V[3][2], int64_t max_n, const uint32_t* d_n, int lo,
                    int hi, uint32_t* hist, uint32_t* scan_scratch, uint32_t* flags, hipStream_t st,
                    hipError_t* err);
+// The same of block ids below digits (at most kWideDigits) in one pass,
+// V[word][0] to V[word][1], and the range of each id but the last, which is the
+// unused slots'.  False, and nothing launched, where it does not apply or
+// scratch_words is too few for its counts.
+constexpr int64_t kWideDigits = 2048;
+bool wide_sort_kv3(const uint32_t* keys, uint32_t* V[3][2], int64_t max_n, const uint32_t* d_n, int64_t digits,
+                   uint32_t* scratch, int64_t scratch_words, uint32_t* scan_scratch, uint32_t* flags,
+                   int32_t* ranges, hipStream_t st, hipError_t* err);
 
 // bin.hip
 hipError_t launch_bin(Ctx* c, const ViewTable& vt, int N, const RasterParams& rp,
@@ -659,6 +667,7 @@ struct Ctx {
     // part of each tile list a backward reads
     bool lists_lazy, lists_filled;
     int block_side;
+    bool block_keyed;  // ik[block_side] holds their block ids (after the one-pass sort it does not)
     int64_t generation;    // gs_bin_sort calls enqueued so far
 };
 
