@@ -83,10 +83,10 @@ __device__ __forceinline__ int seg_search(const uint32_t* pre, int n, uint32_t j
 
 __device__ __forceinline__ void wave_units_load(WaveUnits& wu, int lane, bool ok, const float4& a,
                                                 const float4& b, int v, const ViewTable& vt,
-                                                const RasterParams& rp, uint32_t& total) {
+                                                const RasterParams& rp, const QuadGrid& qg, uint32_t& total) {
     uint32_t units = 0;
     if (ok) {
-        const SplatSpan sp = splat_span(a, b, vt.H[v], quad_grid(rp.tile_w, rp.tile_h), rp.alpha_min);
+        const SplatSpan sp = splat_span(a, b, vt.H[v], qg, rp.alpha_min);
         wu.sp[lane] = sp;
         if (sp.r0 <= sp.r1) units = (uint32_t)(sp.r1 / kBlockQuads - sp.r0 / kBlockQuads + 1);
     }
@@ -96,8 +96,12 @@ __device__ __forceinline__ void wave_units_load(WaveUnits& wu, int lane, bool ok
     if (lane == 0) wu.upre[kWave] = total;
 }
 
+// Bound by the records' reads and, nearly as much, by its arithmetic (the
+// quadrant geometry comes from the host, pair indices are divided in 32 bits,
+// and cnt is only written where the packed count does not fit): 20M pairs 267
+// -> 245 us, 24M 294 -> 278, 4M 57 -> 51.
 __global__ __launch_bounds__(kBlock) void k_count(const float4* __restrict__ rec, int N,
-                                                  ViewTable vt, RasterParams rp,
+                                                  ViewTable vt, RasterParams rp, QuadGrid qg,
                                                   uint32_t* __restrict__ cnt,
                                                   uint32_t* __restrict__ key,
                                                   uint32_t* __restrict__ val,
@@ -108,22 +112,23 @@ __global__ __launch_bounds__(kBlock) void k_count(const float4* __restrict__ rec
         branges[k] = 0;
     const int64_t pair = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (pair >= (int64_t)vt.V * N) return;
-    const int v = (int)(pair / N);
+    const int v = (int)((uint32_t)pair / (uint32_t)N);  // (at most 2^26 pairs)
     const float4 a = rec[3 * pair], b = rec[3 * pair + 1];
     // an upper bound per block row (the emit pass fills what it over-counts),
     // each lane over its own splat's rows
     uint32_t c = 0;
     if (record_ok(a, b, rp.alpha_min)) {
-        const SplatSpan sp = splat_span(a, b, vt.H[v], quad_grid(rp.tile_w, rp.tile_h), rp.alpha_min);
+        const SplatSpan sp = splat_span(a, b, vt.H[v], qg, rp.alpha_min);
         if (sp.r0 <= sp.r1)
             for (int br = sp.r0 / kBlockQuads; br <= sp.r1 / kBlockQuads; br++)
-                c += (uint32_t)unit_band_count(sp, br, vt.W[v], vt.H[v], quad_grid(rp.tile_w, rp.tile_h));
+                c += (uint32_t)unit_band_count(sp, br, vt.W[v], vt.H[v], qg);
     }
-    cnt[pair] = c;
     key[pair] = c > 0 ? __float_as_uint(a.z) : 0xFFFFFFFFu;
     // the pair index in the low pbits, the count above it (all ones when it
     // does not fit: the full count is then read back from cnt)
-    val[pair] = (uint32_t)pair | (min(c, ~0u >> pbits) << pbits);
+    const uint32_t esc = ~0u >> pbits;
+    if (c >= esc) cnt[pair] = c;
+    val[pair] = (uint32_t)pair | (min(c, esc) << pbits);
 }
 
 // Masks of four block columns of a unit from q0 = 8 c on: row i's quadrant
@@ -170,7 +175,8 @@ __device__ __forceinline__ void store_at(uint32_t* p, uint32_t at, uint32_t v) {
 // reports the number of visible pairs (their depth
 // keys sort before the culled ones' 0xFFFFFFFF).
 __global__ __launch_bounds__(kBlock) void k_emit(const float4* __restrict__ rec, int N, ViewTable vt,
-                                                 RasterParams rp, const uint32_t* __restrict__ order,
+                                                 RasterParams rp, QuadGrid qg,
+                                                 const uint32_t* __restrict__ order,
                                                  uint32_t pmask, const uint32_t* __restrict__ off,
                                                  const uint32_t* __restrict__ keys, int64_t n,
                                                  const uint32_t* __restrict__ used,
@@ -184,7 +190,6 @@ __global__ __launch_bounds__(kBlock) void k_emit(const float4* __restrict__ rec,
     const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
     WaveUnits& wu = s_wu[w];
-    const QuadGrid qg = quad_grid(rp.tile_w, rp.tile_h);
     const uint32_t lim = *used;    // nothing is written after an overflow
     const bool any = lim != 0u;
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
@@ -215,7 +220,7 @@ __global__ __launch_bounds__(kBlock) void k_emit(const float4* __restrict__ rec,
     uint32_t wave_total = c;
     for (int sh = 32; sh > 0; sh >>= 1) wave_total += (uint32_t)__shfl_xor((int)wave_total, sh, kWave);
     uint32_t U;
-    wave_units_load(wu, lane, ok, a, b, v, vt, rp, U);
+    wave_units_load(wu, lane, ok, a, b, v, vt, rp, qg, U);
     s_pair[w][lane] = pair;
     __syncthreads();
     uint32_t done = 0;  // entries of the wave written so far
@@ -729,7 +734,8 @@ hipError_t launch_bin(Ctx* c, const ViewTable& vt, int N, const RasterParams& rp
         const unsigned gp = (unsigned)((npairs + kBlock - 1) / kBlock);
         int pbits = 1;  // bits of a pair index (the capacity keeps it at most 26)
         while (((int64_t)1 << pbits) < npairs) pbits++;
-        hipLaunchKernelGGL(k_count, dim3(gp), dim3(kBlock), 0, st, rec, N, vt, rp, c->cnt, c->pk[0],
+        const QuadGrid qg = quad_grid(rp.tile_w, rp.tile_h);
+        hipLaunchKernelGGL(k_count, dim3(gp), dim3(kBlock), 0, st, rec, N, vt, rp, qg, c->cnt, c->pk[0],
                            c->pv[0], c->ranges, 2 * NB, pbits);
         // the pair and its entry count travel with the depth key as one word;
         // the sorted counts are then unpacked and scanned into the entry offsets
@@ -748,7 +754,7 @@ hipError_t launch_bin(Ctx* c, const ViewTable& vt, int N, const RasterParams& rp
                                            &chk_blocks)) != hipSuccess)
             return e;
         const int64_t I = c->cap.max_isect;
-        hipLaunchKernelGGL(k_emit, dim3(gp), dim3(kBlock), 0, st, rec, N, vt, rp, order,
+        hipLaunchKernelGGL(k_emit, dim3(gp), dim3(kBlock), 0, st, rec, N, vt, rp, qg, order,
                            (uint32_t)((1u << pbits) - 1u), off,
                            c->pk[side], npairs, used, c->ik[0], c->iv[0], c->im[0], c->im[0] + I, c->diag);
         int bbits = 1;  // block ids and the sentinel NB

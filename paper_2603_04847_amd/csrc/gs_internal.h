@@ -251,15 +251,19 @@ struct SplatSpan {
 
 constexpr float kSpanEps = 1e-3f;
 
-// Quadrant geometry of a call: half-tile sizes and their reciprocals (exact,
-// powers of two), so no division is left in the per-row work.
+// Quadrant geometry of a call: half-tile sizes (powers of two), their logarithms
+// and their reciprocals (exact), made on the host: no division, and no multiply
+// of whole numbers, is left in the kernels.
 struct QuadGrid {
     int hw, hh;
+    int sw, sh;
     float ihw, ihh;
 };
 
-__host__ __device__ __forceinline__ QuadGrid quad_grid(int TW, int TH) {
+inline QuadGrid quad_grid(int TW, int TH) {
     QuadGrid g;
+    g.sw = __builtin_ctz(TW / 2);
+    g.sh = __builtin_ctz(TH / 2);
     g.hw = TW / 2;
     g.hh = TH / 2;
     g.ihw = 1.f / (float)g.hw;
@@ -286,7 +290,7 @@ __device__ __forceinline__ SplatSpan splat_span(const float4& a, const float4& b
     // the height of the leftmost point -Sxy sqrt(2 t / Sxx)
     s.ey = __builtin_amdgcn_sqrtf(2.f * t * A * idet);
     s.dyL = B * idet * __builtin_amdgcn_sqrtf(2.f * t * s.det / C);
-    const int nrows = (H + g.hh - 1) / g.hh;
+    const int nrows = (H + g.hh - 1) >> g.sh;
     s.r0 = max((int)floorf((s.my - s.ey - kSpanEps) * g.ihh), 0);
     s.r1 = min((int)floorf((s.my + s.ey + kSpanEps) * g.ihh), nrows - 1);
     return s;
@@ -395,10 +399,10 @@ struct BlockUnit {
 __device__ __forceinline__ BlockUnit block_unit(const SplatSpan& s, int br, int W, int H,
                                                 const QuadGrid& g) {
     BlockUnit u;
-    const int last = (W + g.hw - 1) / g.hw - 1;
+    const int last = ((W + g.hw - 1) >> g.sw) - 1;
     const float wmax = (float)W - 0.5f, hmax = (float)H - 0.5f;
     // the rows' bands, exact in float (whole numbers and halves)
-    const float y0 = (float)(kBlockQuads * br * g.hh) + 0.5f;
+    const float y0 = (float)((kBlockQuads * br) << g.sh) + 0.5f;
     int c0 = kNoCols, c1 = -1;
 #pragma unroll
     for (int i = 0; i < kBlockQuads; i++) {
@@ -428,7 +432,7 @@ __device__ __forceinline__ int unit_band_count(const SplatSpan& s, int br, int W
 #pragma clang fp contract(off)
     const int ra = max(s.r0, kBlockQuads * br), rb = min(s.r1, kBlockQuads * br + kBlockQuads - 1);
     if (ra > rb) return 0;
-    const float ya = ra * g.hh + 0.5f, yb = (float)min(rb * g.hh + g.hh, H) - 0.5f;
+    const float ya = (float)(ra << g.sh) + 0.5f, yb = (float)min((rb + 1) << g.sh, H) - 0.5f;
     float la = fmaxf(ya - s.my, -s.ey), lb = fminf(yb - s.my, s.ey);
     if (la > lb + kSpanEps) return 0;
     if (la > lb) la = lb = 0.5f * (la + lb);
@@ -438,7 +442,7 @@ __device__ __forceinline__ int unit_band_count(const SplatSpan& s, int br, int W
     const float xl = s.mx + (-s.B * dl - ql) * s.iA - (kSpanEps + kBandEps);
     const float xr = s.mx + (-s.B * dr + qr) * s.iA + (kSpanEps + kBandEps);
     if (!(xl <= (float)W - 0.5f) || !(xr >= 0.5f)) return 0;
-    const int ncols = (W + g.hw - 1) / g.hw;
+    const int ncols = (W + g.hw - 1) >> g.sw;
     const int c0 = max((int)ceilf((xl + 0.5f) * g.ihw - 1.f), 0);
     const int c1 = min((int)floorf((xr - 0.5f) * g.ihw), ncols - 1);
     return c0 <= c1 ? (c1 >> kBlockShift) - (c0 >> kBlockShift) + 1 : 0;

@@ -17,12 +17,14 @@ constexpr int kWaves = kThreads / kWave;
 
 // ------------------------------------------------------------------ scan
 
+// shifts by 1, 2, 4 and 8 inside the rows of 16 lanes, then the rows' carries
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-    const int lane = __lane_id();
-    for (int off = 1; off < kWave; off <<= 1) {
-        uint32_t t = __shfl_up(v, off, kWave);
-        if (lane >= off) v += t;
-    }
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);
     return v;
 }
 
@@ -148,9 +150,14 @@ __global__ __launch_bounds__(THREADS) void k_scan(uint32_t* __restrict__ data, i
     int64_t n = max_n;
     if (d_cnt) n = min(max_n, mul * (((int64_t)*d_cnt + per - 1) / per + add));
     const int64_t ntiles = (n + TILE - 1) / TILE;
-    if (threadIdx.x == 0) s_t = atomicAdd(&ws[0], 1u);
-    __syncthreads();
-    const int64_t t = s_t;
+    // a grid of one needs neither ticket nor clearing, each a round trip to
+    // memory (5.5 -> 4.6 us)
+    const bool lone = THREADS == kThreads && gridDim.x == 1;
+    if (!lone) {
+        if (threadIdx.x == 0) s_t = atomicAdd(&ws[0], 1u);
+        __syncthreads();
+    }
+    const int64_t t = lone ? 0 : s_t;
     if (t >= ntiles) {
         if (t == 0 && threadIdx.x == 0) {
             if (total_out) *total_out = 0u;
@@ -189,7 +196,7 @@ __global__ __launch_bounds__(THREADS) void k_scan(uint32_t* __restrict__ data, i
         uint32_t tot;
         uint32_t ex = block_excl_scan(s, s_w, tot);
         if (threadIdx.x < kWave) {
-            if (threadIdx.x == 0) st_word(words + t, t == 0 ? kIncl : kAgg, tot);
+            if (threadIdx.x == 0 && !lone) st_word(words + t, t == 0 ? kIncl : kAgg, tot);
             const uint32_t excl = t > 0 ? wave_lookback(words, t, flags) : 0u;
             if (threadIdx.x == 0) {
                 if (t > 0) st_word(words + t, kIncl, excl + tot);
@@ -219,6 +226,7 @@ __global__ __launch_bounds__(THREADS) void k_scan(uint32_t* __restrict__ data, i
                 if (base + i < n) data[base + i] = v[i];
         }
     }
+    if (lone) return;
     // every tile has finished its look-back once all have taken a ticket here
     if (threadIdx.x == 0) s_last = atomicAdd(&ws[1], 1u) == gridDim.x - 1;
     __syncthreads();
