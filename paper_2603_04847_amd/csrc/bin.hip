@@ -738,21 +738,28 @@ hipError_t launch_bin(Ctx* c, const ViewTable& vt, int N, const RasterParams& rp
         hipLaunchKernelGGL(k_count, dim3(gp), dim3(kBlock), 0, st, rec, N, vt, rp, qg, c->cnt, c->pk[0],
                            c->pv[0], c->ranges, 2 * NB, pbits);
         // the pair and its entry count travel with the depth key as one word;
-        // the sorted counts are then unpacked and scanned into the entry offsets
-        const int side = radix_sort_pairs(c->pk[0], c->pv[0], c->pk[1], c->pv[1], npairs, nullptr, 0, 32,
-                                          c->hist, c->scan_scratch, c->diag + kDiagFlags, st, &e);
-        if (e != hipSuccess) return e;
-        const uint32_t* order = c->pv[side];
+        // the sorted counts are then unpacked and scanned into the entry offsets,
+        // whose total is checked against the capacity
         uint32_t* off = c->off;
         uint32_t* total = c->scalars + 0;
         uint32_t* used = c->scalars + 1;
-        // the counts, unpacked as the scan loads them; its last tile checks
-        // the block-entry total against the capacity
         const CapCheck chk_blocks = {c->cap.max_isect, used, c->diag, nullptr, nullptr};
-        const ScanUnpack un = {order, c->cnt, pbits};
-        if ((e = exclusive_scan_u32_unpack(off, un, npairs, total, c->scan_scratch, c->diag + kDiagFlags, st,
-                                           &chk_blocks)) != hipSuccess)
-            return e;
+        int side = 1;
+        if (npairs <= kSmallSort) {  // see k_small_sort
+            const ScanUnpack un = {c->pv[0], c->cnt, pbits};
+            e = small_sort_scan(c->pk[0], c->pk[1], c->pv[1], npairs, un, off, total, c->diag + kDiagFlags, st,
+                                chk_blocks);
+            if (e != hipSuccess) return e;
+        } else {
+            side = radix_sort_pairs(c->pk[0], c->pv[0], c->pk[1], c->pv[1], npairs, nullptr, 0, 32, c->hist,
+                                    c->scan_scratch, c->diag + kDiagFlags, st, &e);
+            if (e != hipSuccess) return e;
+            const ScanUnpack un = {c->pv[side], c->cnt, pbits};
+            if ((e = exclusive_scan_u32_unpack(off, un, npairs, total, c->scan_scratch, c->diag + kDiagFlags, st,
+                                               &chk_blocks)) != hipSuccess)
+                return e;
+        }
+        const uint32_t* order = c->pv[side];
         const int64_t I = c->cap.max_isect;
         hipLaunchKernelGGL(k_emit, dim3(gp), dim3(kBlock), 0, st, rec, N, vt, rp, qg, order,
                            (uint32_t)((1u << pbits) - 1u), off,

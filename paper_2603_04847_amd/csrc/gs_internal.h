@@ -495,7 +495,14 @@ size_t radix_hist_words(int64_t max_n);
 int radix_sort_pairs(uint32_t* ka, uint32_t* va, uint32_t* kb, uint32_t* vb, int64_t max_n,
                      const uint32_t* d_n, int lo, int hi, uint32_t* hist, uint32_t* scan_scratch,
                      uint32_t* flags, hipStream_t st, hipError_t* err);
-// The same with three value words per item (separate arrays): K[side],
+// At most kSmallSort pairs, of keys and packed words un.src, sorted by key into
+// kout and vout, and the scan of their counts (exclusive_scan_u32_unpack's) into
+// off, in one launch.  Culled pairs' keys are all ones.
+constexpr int64_t kSmallSort = 16384;
+hipError_t small_sort_scan(const uint32_t* keys, uint32_t* kout, uint32_t* vout, int64_t n, const ScanUnpack& un,
+                           uint32_t* off, uint32_t* total_out, uint32_t* flags, hipStream_t st,
+                           const CapCheck& chk);
+// radix_sort_pairs with three value words per item (separate arrays): K[side],
 // V[word][side]; returns the side holding the result.
 int radix_sort_kv3(uint32_t* K[2], uint32_t* V[3][2], int64_t max_n, const uint32_t* d_n, int lo,
                    int hi, uint32_t* hist, uint32_t* scan_scratch, uint32_t* flags, hipStream_t st,

@@ -646,6 +646,160 @@ __global__ __launch_bounds__(kWideBlock, 4) void k_wide_scatter(
         }
 }
 
+// ------------------------------------------------------------------ a small sort in one workgroup
+//
+// At most kSmallSort packed pairs sorted by depth key and their entry counts
+// scanned, all in one workgroup's LDS: where the general path is four passes
+// of three launches and a scan, each a few microseconds whatever its size.
+// Keys are taken from the smallest visible one up, the culled pairs' just past
+// the largest, so the digits cover the range there is: three passes of nine
+// bits for a depth range of sixteen octaves.  Every wave owns a run of
+// 64 `steps` items, as in k_radix_scatter; places past the end are culled keys,
+// which sort last.  Bound by one CU's arithmetic (the ballots of the ranks): 2000
+// pairs 58 -> 16 us of kernels, 10000 75 -> 36, 16384 67 -> 52, each in one
+// launch instead of thirteen; what the LDS holds is the limit.
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallWaves = kSmallThreads / kWave;
+constexpr int kSmallItems = (int)(kSmallSort / kSmallThreads);
+constexpr int kSmallBits = 9;
+constexpr int kSmallDigits = 1 << kSmallBits;
+
+__global__ __launch_bounds__(kSmallThreads) void k_small_sort(const uint32_t* __restrict__ kin,
+                                                              uint32_t* __restrict__ kout,
+                                                              uint32_t* __restrict__ vout, int n, int steps,
+                                                              ScanUnpack un, uint32_t* __restrict__ off,
+                                                              uint32_t* __restrict__ total_out,
+                                                              uint32_t* __restrict__ flags, CapCheck chk) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t s_items[];  // [2][1024 steps]
+    __shared__ uint16_t s_cnt[kSmallWaves][kSmallDigits];
+    __shared__ uint32_t s_w[kSmallWaves], s_lo[kSmallWaves], s_hi[kSmallWaves];
+    uint32_t* s_key = s_items;
+    uint32_t* s_val = s_items + kSmallThreads * steps;
+    const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
+    const int first = w * kWave * steps + lane;  // item i of the thread: first + 64 i
+    uint32_t k[kSmallItems], v[kSmallItems], rank[kSmallItems];
+    uint32_t lo = ~0u, hi = 0u;
+#pragma unroll
+    for (int i = 0; i < kSmallItems; i++) {
+        if (i < steps) {
+            const int j = first + i * kWave;
+            k[i] = j < n ? kin[j] : ~0u;
+            v[i] = j < n ? un.src[j] : 0u;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kSmallItems; i++) {
+        if (i < steps) {
+            lo = min(lo, k[i]);
+            hi = max(hi, k[i] == ~0u ? 0u : k[i]);
+        }
+    }
+    for (int m = 32; m > 0; m >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, m, kWave));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, m, kWave));
+    }
+    if (lane == 0) {
+        s_lo[w] = lo;
+        s_hi[w] = hi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kSmallWaves; q++) {
+        lo = min(lo, s_lo[q]);
+        hi = max(hi, s_hi[q]);
+    }
+    const uint32_t top = lo == ~0u ? 0u : hi - lo + 1u;  // a culled pair's key
+    const int width = top ? 32 - __clz((int)top) : 0;
+    const int passes = (width + kSmallBits - 1) / kSmallBits;
+    const int bits = passes ? (width + passes - 1) / passes : 0;
+#pragma unroll
+    for (int i = 0; i < kSmallItems; i++)
+        if (i < steps) k[i] = k[i] == ~0u ? top : k[i] - lo;
+    for (int p = 0; p < passes; p++) {
+        const int shift = p * bits;
+        const uint32_t mask = (1u << bits) - 1u;
+        for (int d = tid; d < kSmallWaves * kSmallDigits / 2; d += kSmallThreads)
+            reinterpret_cast<uint32_t*>(&s_cnt[0][0])[d] = 0u;
+        __syncthreads();
+        // stable rank inside the wave's run: earlier steps (LDS count) + earlier lanes
+#pragma unroll
+        for (int i = 0; i < kSmallItems; i++) {
+            if (i < steps) {
+                const uint32_t d = (k[i] >> shift) & mask;
+                const uint64_t peers = match_digit(d, true, bits);
+                const uint32_t before = s_cnt[w][d];
+                const uint32_t below = (uint32_t)__popcll(peers & lanemask_lt());
+                rank[i] = before + below;
+                if (below == 0) s_cnt[w][d] = (uint16_t)(before + (uint32_t)__popcll(peers));
+            }
+        }
+        __syncthreads();
+        // a digit a thread: offsets of the waves after the smaller digits' items
+        uint32_t c[kSmallWaves], run = 0;
+        if (tid < kSmallDigits)
+#pragma unroll
+            for (int q = 0; q < kSmallWaves; q++) {
+                c[q] = run;
+                run += s_cnt[q][tid];
+            }
+        uint32_t tot;
+        const uint32_t start = block_excl_scan(run, s_w, tot);
+        if (tid < kSmallDigits)
+#pragma unroll
+            for (int q = 0; q < kSmallWaves; q++) s_cnt[q][tid] = (uint16_t)(start + c[q]);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kSmallItems; i++) {
+            if (i < steps) {
+                const uint32_t to = s_cnt[w][(k[i] >> shift) & mask] + rank[i];
+                s_key[to] = k[i];
+                s_val[to] = v[i];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kSmallItems; i++) {
+            if (i < steps) {
+                k[i] = s_key[first + i * kWave];
+                v[i] = s_val[first + i * kWave];
+            }
+        }
+    }
+    // the sorted pairs, and the scan of their counts
+    const uint32_t esc = ~0u >> un.pbits, pmask = (1u << un.pbits) - 1u;
+    uint32_t sum = 0;
+#pragma unroll
+    for (int i = 0; i < kSmallItems; i++) {
+        if (i < steps) {
+            const int j = first + i * kWave;
+            uint32_t c = v[i] >> un.pbits;
+            if (c == esc) c = un.cnt[v[i] & pmask];
+            const uint32_t inc = wave_incl_scan(c);
+            rank[i] = sum + inc - c;
+            sum += (uint32_t)bcast((int)inc, kWave - 1);
+            if (j < n) {
+                kout[j] = k[i] == top ? ~0u : k[i] + lo;
+                vout[j] = v[i];
+            }
+        }
+    }
+    if (lane == 0) s_w[w] = sum;
+    __syncthreads();
+    uint32_t base = 0, total = 0;
+#pragma unroll
+    for (int q = 0; q < kSmallWaves; q++) {
+        base += q < w ? s_w[q] : 0u;
+        total += s_w[q];
+    }
+#pragma unroll
+    for (int i = 0; i < kSmallItems; i++)
+        if (i < steps && first + i * kWave < n) off[first + i * kWave] = base + rank[i];
+    if (tid == 0) {
+        *total_out = total;
+        cap_check(total, chk, flags);
+    }
+}
+
 }  // namespace
 
 size_t scan_scratch_words(int64_t max_n) {
@@ -823,6 +977,16 @@ bool wide_sort_kv3(const uint32_t* keys, uint32_t* V[3][2], int64_t max_n, const
     else scatter(k_wide_scatter<11>);
     *err = hipGetLastError();
     return true;
+}
+
+hipError_t small_sort_scan(const uint32_t* keys, uint32_t* kout, uint32_t* vout, int64_t n, const ScanUnpack& un,
+                           uint32_t* off, uint32_t* total_out, uint32_t* flags, hipStream_t st,
+                           const CapCheck& chk) {
+    if (n < 1 || n > kSmallSort) return hipErrorInvalidValue;
+    const int steps = (int)((n + kSmallThreads - 1) / kSmallThreads);
+    hipLaunchKernelGGL(k_small_sort, dim3(1), dim3(kSmallThreads), 2 * sizeof(uint32_t) * kSmallThreads * steps, st,
+                       keys, kout, vout, (int)n, steps, un, off, total_out, flags, chk);
+    return hipGetLastError();
 }
 
 }  // namespace gs
