@@ -232,6 +232,9 @@ def _stream(stream=None):
     return torch.cuda.current_stream().cuda_stream
 
 
+stream_of = _stream  # for callers that make several calls on one stream
+
+
 def default_settings(**over):
     s = gs_settings()
     load().gs_default_settings(ctypes.byref(s))
@@ -261,8 +264,8 @@ class Cameras:
         self.wh = np.ascontiguousarray(np.asarray(wh, dtype=np.int32).reshape(-1, 2))
         self.V = self.wh.shape[0]
         self.index = None if index is None else np.ascontiguousarray(index, dtype=np.int32)
-        self._c = gs_cameras(_ptr(viewmat), _ptr(intr), self.wh.ctypes.data_as(c_vp), self.V,
-                             None if self.index is None else self.index.ctypes.data_as(c_vp))
+        self._c = gs_cameras(_ptr(viewmat), _ptr(intr), self.wh.ctypes.data, self.V,
+                             None if self.index is None else self.index.ctypes.data)
 
     @property
     def struct(self):
@@ -270,7 +273,7 @@ class Cameras:
 
     @property
     def n_pixels(self):
-        return int((self.wh[:, 0].astype("int64") * self.wh[:, 1]).sum())
+        return sum(w * h for w, h in self.wh.tolist())
 
 
 class Context:

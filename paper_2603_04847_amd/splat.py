@@ -42,6 +42,7 @@ class Splatter:
     def forward(self, params, sh_degree, viewmat, intr, wh, stream=None):
         """params: dict of device tensors (planar layouts); viewmat [V,12], intr [V,4]
         device; wh [V,2] host.  Returns (rgb [P,3], T_final [P], last [P], cams)."""
+        stream = L.stream_of(stream)
         cams = L.Cameras(_dev(viewmat), _dev(intr), wh)
         g = L.make_gaussians(*(params[k] for k in PARAM_KEYS), sh_degree)
         dev = viewmat.device
@@ -84,10 +85,12 @@ class RasterizeGaussians(torch.autograd.Function):
                 wh, sh_degree, splatter):
         params = dict(means=_dev(means), log_scales=_dev(log_scales), quats=_dev(quats),
                       opacity_logit=_dev(opacity_logit), sh=_dev(sh))
-        tw = _dev(twist)
-        viewmat = torch.empty_like(_dev(base_viewmat))
-        L.gs_pose_compose(tw, _dev(base_viewmat), viewmat)
-        rgb, T, last, cams = splatter.forward(params, sh_degree, viewmat, intr, wh)
+        # (the stream is looked up once a pass, here and in the other methods)
+        stream = L.stream_of()
+        tw, base = _dev(twist), _dev(base_viewmat)
+        viewmat = torch.empty_like(base)
+        L.gs_pose_compose(tw, base, viewmat, stream)
+        rgb, T, last, cams = splatter.forward(params, sh_degree, viewmat, intr, wh, stream)
         actx.splatter = splatter
         actx.sh_degree = sh_degree
         actx.cams = cams
@@ -102,13 +105,14 @@ class RasterizeGaussians(torch.autograd.Function):
     def backward(actx, v_rgb, _vT, _vlast):
         tw, T, last, *pv = actx.saved_tensors
         params = dict(zip(PARAM_KEYS, pv))
+        stream = L.stream_of()
         if actx.splatter.ctx.generation() != actx.generation:
-            actx.splatter.rebin(params, actx.sh_degree, actx.cams)
+            actx.splatter.rebin(params, actx.sh_degree, actx.cams, stream)
         grads, v_tw_cur = actx.splatter.backward(params, actx.sh_degree, actx.cams, T, last,
-                                                 v_rgb.contiguous())
+                                                 v_rgb.contiguous(), stream=stream)
         actx.generation = actx.splatter.ctx.generation()
         v_tw = torch.empty_like(tw)
-        L.gs_pose_compose_bwd(tw, v_tw_cur, v_tw)
+        L.gs_pose_compose_bwd(tw, v_tw_cur, v_tw, stream)
         return (grads["means"], grads["log_scales"], grads["quats"], grads["opacity_logit"],
                 grads["sh"], v_tw, None, None, None, None, None)
 
@@ -119,16 +123,20 @@ class TrackReprojection(torch.autograd.Function):
     @staticmethod
     def forward(actx, X, twist, base_viewmat, intr, obs_cam, obs_pt, obs_xy, delta, lam, ctx,
                 near_plane=0.01):
-        tw = _dev(twist)
-        viewmat = torch.empty_like(_dev(base_viewmat))
-        L.gs_pose_compose(tw, _dev(base_viewmat), viewmat)
+        stream = L.stream_of()
+        tw, base, X = _dev(twist), _dev(base_viewmat), _dev(X)
+        viewmat = torch.empty_like(base)
+        L.gs_pose_compose(tw, base, viewmat, stream)
         loss = torch.zeros((1,), device=X.device, dtype=torch.float32)
-        v_X = torch.zeros_like(_dev(X))
-        v_tw_cur = torch.zeros_like(tw)
-        L.track_reproj_fwd_bwd(ctx, _dev(X), viewmat, _dev(intr), obs_cam, obs_pt, _dev(obs_xy),
-                               delta, lam, near_plane, loss, v_X, v_tw_cur)
+        # the gradients the kernels add to, one buffer cleared by one fill (the
+        # loss, which the caller gets and may change in place, is its own)
+        acc = torch.zeros((X.numel() + tw.numel(),), device=X.device, dtype=torch.float32)
+        v_X = acc[:X.numel()].view_as(X)
+        v_tw_cur = acc[X.numel():].view_as(tw)
+        L.track_reproj_fwd_bwd(ctx, X, viewmat, _dev(intr), obs_cam, obs_pt, _dev(obs_xy),
+                               delta, lam, near_plane, loss, v_X, v_tw_cur, stream=stream)
         v_tw = torch.empty_like(tw)
-        L.gs_pose_compose_bwd(tw, v_tw_cur, v_tw)
+        L.gs_pose_compose_bwd(tw, v_tw_cur, v_tw, stream)
         actx.save_for_backward(v_X, v_tw)
         return loss[0]
 
