@@ -10,18 +10,14 @@
 //   d SSIM / d x(q) = sum_p w(p - q) [dS/dmu_x(p) + 2 x(q) dS/dE_xx(p)
 //                                      + y(q) dS/dE_xy(p)] / (3 P_v V).
 // A workgroup owns a 32 x 32 tile of one view and keeps everything in LDS:
-// the images with a 10-pixel halo, their four window sums over the tile plus
-// a 5-pixel ring (mu_x, mu_y, E_xy and E_xx + E_yy, which S has only as their
-// sum; separable: a horizontal pass, then a vertical one), the
+// the images with a 10-pixel halo, their five window sums over the tile plus
+// a 5-pixel ring (separable: a horizontal pass, then a vertical one), the
 // partial derivatives there (zero outside the image: the sum runs over image
 // pixels only), and their window sums over the tile.  Nothing but the images
 // and the gradient crosses HBM; the ring's window sums are computed again by
 // the neighbouring tiles.  Each thread walks a run of consecutive outputs of
 // one row or column with the window's inputs in registers, so every LDS value
-// it loads serves up to 11 taps.  Bound by the window sums' multiply-adds (288 a
-// pixel and channel with five sums about zero, 245 with four about the tile's
-// mean): 4 uneven views of about 979 x 545 107 -> 102 us, 4 of 1600 x 1066 380 -> 349, and the
-// gradient's error against 64 bits 2.7e-6 -> 1.0e-6 of its rms.
+// it loads serves up to 11 taps.
 #include <math.h>
 
 #include "gs_internal.h"
@@ -55,14 +51,14 @@ struct PhotoArgs {
 };
 
 // LDS: the two images of one channel (kIn x kIn each), then a region that
-// holds the four horizontal window sums (kIn rows x kMid columns) and later,
+// holds the five horizontal window sums (kIn rows x kMid columns) and later,
 // after a barrier, the three partial-derivative maps (kMid x kMid) and their
 // horizontal window sums (kMid rows x kT columns).
 struct PhotoLds {
     float X[kIn][kIn + 3];  // columns kIn.. are read only for outputs past kMid
     float Y[kIn][kIn + 3];
     union {
-        float H[4][kIn][kMid + 1];
+        float H[5][kIn][kMid + 1];
         struct {
             float D[3][kMid][kMid + 1];
             float E[3][kMid][kT + 1];
@@ -131,12 +127,7 @@ __global__ __launch_bounds__(kThreads) void k_photo(PhotoArgs a, Window win) {
             }
         }
         __syncthreads();
-        // the squares and products are taken about the tile's mean (of 8 x 8
-        // samples, every wave for itself): variances do not depend on it, and
-        // less cancels in them than about zero
-        const int sr = kIn / 16 + kIn / 8 * (tid % kWave / 8), sc = kIn / 16 + kIn / 8 * (tid % 8);
-        const float ax = wave_sum(s.X[sr][sc]) * (1.f / kWave), ay = wave_sum(s.Y[sr][sc]) * (1.f / kWave);
-        // ---- horizontal window sums of x, y, x^2 + y^2, x y: every row of the
+        // ---- horizontal window sums of x, y, x^2, y^2, x y: every row of the
         // halo, columns of the tile plus the ring
         // consecutive lanes take consecutive rows at one column run: the odd
         // row strides (53, 43 words) put their LDS words in distinct banks
@@ -145,31 +136,33 @@ __global__ __launch_bounds__(kThreads) void k_photo(PhotoArgs a, Window win) {
             const int r = item % kIn, c0 = (item / kIn) * kRunH;
             // the run's inputs and their squares and products, formed once
             float xs[kRunH + kTaps - 1], ys[kRunH + kTaps - 1];
-            float ee[kRunH + kTaps - 1], xy[kRunH + kTaps - 1];
+            float xx[kRunH + kTaps - 1], yy[kRunH + kTaps - 1], xy[kRunH + kTaps - 1];
 #pragma unroll
             for (int k = 0; k < kRunH + kTaps - 1; k++) {
                 xs[k] = s.X[r][c0 + k];
                 ys[k] = s.Y[r][c0 + k];
-                const float xc = xs[k] - ax, yc = ys[k] - ay;
-                ee[k] = __builtin_fmaf(xc, xc, yc * yc);
-                xy[k] = xc * yc;
+                xx[k] = xs[k] * xs[k];
+                yy[k] = ys[k] * ys[k];
+                xy[k] = xs[k] * ys[k];
             }
 #pragma unroll
             for (int j = 0; j < kRunH; j++) {
                 if (c0 + j >= kMid) break;
-                float m0 = 0.f, m1 = 0.f, m2 = 0.f, m3 = 0.f;
+                float m0 = 0.f, m1 = 0.f, m2 = 0.f, m3 = 0.f, m4 = 0.f;
 #pragma unroll
                 for (int k = 0; k < kTaps; k++) {
                     const float g = win.g[k];
                     m0 = __builtin_fmaf(g, xs[j + k], m0);
                     m1 = __builtin_fmaf(g, ys[j + k], m1);
-                    m2 = __builtin_fmaf(g, ee[j + k], m2);
-                    m3 = __builtin_fmaf(g, xy[j + k], m3);
+                    m2 = __builtin_fmaf(g, xx[j + k], m2);
+                    m3 = __builtin_fmaf(g, yy[j + k], m3);
+                    m4 = __builtin_fmaf(g, xy[j + k], m4);
                 }
                 s.u.H[0][r][c0 + j] = m0;
                 s.u.H[1][r][c0 + j] = m1;
                 s.u.H[2][r][c0 + j] = m2;
                 s.u.H[3][r][c0 + j] = m3;
+                s.u.H[4][r][c0 + j] = m4;
             }
         }
         __syncthreads();
@@ -186,9 +179,9 @@ __global__ __launch_bounds__(kThreads) void k_photo(PhotoArgs a, Window win) {
             for (int j = 0; j < kRunA; j++) dv[u][j][0] = dv[u][j][1] = dv[u][j][2] = 0.f;
             if (item < kItemsA) {
                 const int c = item % kMid, r0 = (item / kMid) * kRunA;
-                float mm[4][kRunA];
+                float mm[5][kRunA];
 #pragma unroll
-                for (int m = 0; m < 4; m++) {
+                for (int m = 0; m < 5; m++) {
                     float col[kRunA + kTaps - 1];
 #pragma unroll
                     for (int k = 0; k < kRunA + kTaps - 1; k++) col[k] = s.u.H[m][r0 + k][c];
@@ -206,13 +199,13 @@ __global__ __launch_bounds__(kThreads) void k_photo(PhotoArgs a, Window win) {
                     const int py = y0 - kR + r0 + j;
                     if (px < 0 || px >= W || py < 0 || py >= H) continue;  // not an image pixel
                     const float mx = mm[0][j], my = mm[1][j];
-                    const float cx = mx - ax, cy = my - ay;
-                    const float sxy = mm[3][j] - cx * cy;
+                    const float sxx = mm[2][j] - mx * mx, syy = mm[3][j] - my * my;
+                    const float sxy = mm[4][j] - mx * my;
                     const float A1 = 2.f * mx * my + kC1, A2 = 2.f * sxy + kC2;
-                    const float B1 = mx * mx + my * my + kC1, B2 = mm[2][j] - (cx * cx + cy * cy) + kC2;
+                    const float B1 = mx * mx + my * my + kC1, B2 = sxx + syy + kC2;
                     const float iD = 1.f / (B1 * B2);
                     const float S = A1 * A2 * iD;
-                    // dS/dmu_x (through mu_x and the mu_x terms of the variances),
+                    // dS/dmu_x (through mu_x and the mu_x terms of s_xx, s_xy),
                     // dS/dE_xx, dS/dE_xy
                     dv[u][j][0] = 2.f * (my * (A2 - A1) - mx * S * (B2 - B1)) * iD;
                     dv[u][j][1] = -S / B2;
