@@ -628,6 +628,17 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t st);
 
 // The context (workspace), shared by the launchers.
 constexpr int kScalarPlan = 8;
+// The raster backward: the segments of a heavy tile at most (twice as many where
+// every tile is taken so: up to 2^18 pixels' worth of them), the heavy tiles at
+// most, and the floats of the pixel states between the segments.
+constexpr int kBwdSegs = 8;
+constexpr int kBwdHeavy = 1366;
+inline size_t snap_floats(int64_t max_tiles) {
+    const int64_t heavy = (max_tiles < kBwdHeavy ? max_tiles : kBwdHeavy) * (kBwdSegs - 1) * 2 * 512;
+    const int64_t px = max_tiles * 512 < (1 << 18) ? max_tiles * 512 : 1 << 18;
+    const int64_t all = px * (2 * kBwdSegs - 1) * 2;
+    return (size_t)(heavy > all ? heavy : all);
+}
 struct Ctx {
     gs_capacity cap;
     int device;
@@ -660,6 +671,7 @@ struct Ctx {
     int32_t* tile_evals;   // [max_tiles] (pixel, entry) evaluations up to the last contributors
     uint32_t* hist;        // radix histograms
     uint32_t* scan_scratch;
+    float* snap;           // [snap_floats] pixel states between the backward's segments
     uint32_t* scalars;     // small device counters (from kScalarPlan: the raster backward's plan)
     double* twist_render;  // [max_views][6]
     double* twist_track;   // [max_cams][6]

@@ -382,12 +382,26 @@ struct BwdArgs {
     const float* v_rgb;
     float* grad_geo;
     float* grad_col;
+    float* snap;  // pixel states at the segments' ends (see chain_bwd)
+    int segs;     // segments of a heavy tile at most
     RasterParams rp;
 };
 
-// Tile t, all of it by one wave.
-template <int TW, int TH>
-__device__ __forceinline__ void tile_bwd(const BwdArgs& g, const ViewTable& vt, int t, BatchLds& sb) {
+// A heavy tile's list is walked in at most g.segs segments of whole batches.
+__device__ __forceinline__ int seg_length(const BwdArgs& g, int lmax) {
+    return ((lmax + g.segs - 1) / g.segs + kWave - 1) / kWave * kWave;
+}
+// the states at the end of segment `seg` of the heavy tile in slot `slot`: [2][pixels]
+template <int PIXELS>
+__device__ __forceinline__ float* snap_at(const BwdArgs& g, int slot, int seg) {
+    return g.snap + ((int64_t)slot * (g.segs - 1) + seg) * (2 * PIXELS);
+}
+
+// Tile t by one wave: all of it, or (SEG) segment `seg` of the heavy tile in
+// slot `slot`, whose pixels start from the states that the chain left.
+template <int TW, int TH, bool SEG>
+__device__ __forceinline__ void tile_bwd(const BwdArgs& g, const ViewTable& vt, int t, BatchLds& sb, int slot = 0,
+                                         int seg = 0) {
     using TM = TileMap<TW, TH>;
     constexpr int PPL = TM::PPL;
     const float4* __restrict__ rec = g.rec;
@@ -436,7 +450,20 @@ __device__ __forceinline__ void tile_bwd(const BwdArgs& g, const ViewTable& vt, 
     lmax = min(lmax, e - s);  // a pixel's last contributor lies inside its tile's list
     if (lmax <= 0) return;
     const float amin = g.rp.alpha_min, amax = g.rp.alpha_max;
-    const int top = s + lmax;  // entries [s, top) can matter
+    int low = s, top = s + lmax;  // entries [s, top) can matter; this wave's are [low, top)
+    if (SEG) {
+        const int len = seg_length(g, lmax), end = (seg + 1) * len;
+        if (seg * len >= lmax) return;
+        low = s + seg * len;
+        top = min(top, s + end);
+        const float* snap = snap_at<TW * TH>(g, slot, seg);
+#pragma unroll
+        for (int k = 0; k < PPL; k++)
+            if (end < min(Lk[k], e - s)) {  // wave-uniform: the slot's pixels reach past the end
+                Tc[k] = snap[k * kWave + lane];
+                VS[k] = snap[TW * TH + k * kWave + lane];
+            }
+    }
     // The gradient component this lane adds after the wave sums E of two splats
     // (the first in lanes 0-31, the second in 32-63; see wave_sums_t): 0 mean.x,
     // 1 mean.y, 2 A, 3 B, 4 C, 5 opacity, 6 r, 7 g, 8 b, -1 none.
@@ -449,20 +476,20 @@ __device__ __forceinline__ void tile_bwd(const BwdArgs& g, const ViewTable& vt, 
     const float kE = comp >= 5 ? 1.f : 0.f;
     const float ua = comp == 0 ? 2.f : 0.f, ub = comp == 1 ? 1.f : 0.f;
     const float vb = comp == 0 ? 1.f : 0.f, vc = comp == 1 ? 2.f : 0.f;
-    int b = s + ((lmax - 1) / kWave) * kWave;
+    int b = low + ((top - low - 1) / kWave) * kWave;
     // the same two-deep pipeline as the forward, walking down: the batches
     // after the first (partial) one are full
     uint32_t id_cur = batch_ids(ids, b, s, top);
     uint32_t id_nxt = batch_ids(ids, b - kWave, s, top);
     LaneSplat ls_cur = {};
     if (lane < top - b) ls_cur = load_splat(rec, id_cur & kPairMask);
-    for (; b >= s; b -= kWave) {
+    for (; b >= low; b -= kWave) {
         const uint32_t id = id_cur;
         const int nb = min(kWave, top - b);
         wave_lds_sync();  // the previous batch is read
         stage_splat(sb, ls_cur);
         ls_cur = {};
-        if (b - kWave >= s) ls_cur = load_splat(rec, id_nxt & kPairMask);
+        if (b - kWave >= low) ls_cur = load_splat(rec, id_nxt & kPairMask);
         id_cur = id_nxt;
         id_nxt = batch_ids(ids, b - 2 * kWave, s, top);
         wave_lds_sync();
@@ -748,10 +775,15 @@ __global__ __launch_bounds__(64) void k_render_fwd_part(const float4* __restrict
     }
 }
 
-// Part `part` of tile t by one wave.
+// What the pixels of part `part` of heavy tile t carry down the list, their
+// transmittance Tc and VS, without the gradients: left at each segment's end
+// (`snap`), from where the segments are then walked at once.  A tile's sums are
+// those of a wave with the whole tile, bit for bit: a wave a part, each adding
+// its own sums, is as exact but rounds otherwise, and what cancels in the
+// sums of needle-like splats made that 1e-3 of the gradients' rms on single ones.
 template <int TW, int TH>
-__device__ __forceinline__ void part_bwd(const BwdArgs& g, const ViewTable& vt, int t, int part,
-                                         BatchLds& sb, PartRing<kPullBwd>& ring) {
+__device__ __forceinline__ void chain_bwd(const BwdArgs& g, const ViewTable& vt, int t, int part, int slot,
+                                          BatchLds& sb, PartRing<kPullBwd>& ring) {
     using TM = TileMap<TW, TH>;
     const float4* __restrict__ rec = g.rec;
     const int32_t* __restrict__ ids = g.ids;
@@ -778,21 +810,30 @@ __device__ __forceinline__ void part_bwd(const BwdArgs& g, const ViewTable& vt, 
     }
     float VS = Tc * (V0 * b0 + V1 * b1 + V2 * b2);
     const int s = g.ranges[2 * t], e = g.ranges[2 * t + 1];
+    int most = 0;  // the tile's largest `last`, which sets the segments
+#pragma unroll
+    for (int k = 0; k < TM::PPL; k++) {
+        int kx, ky;
+        TM::pixel(lane, k, kx, ky);
+        kx += tx * TW;
+        ky += ty * TH;
+        if (kx < W && ky < H) most = max(most, g.last[(int64_t)vt.pix_off[v] + (int64_t)ky * W + kx]);
+    }
     // a pixel's last contributor lies inside its tile's list
+    most = min(__builtin_amdgcn_readfirstlane(wave_max_i(most)), e - s);
     const int lmax = min(__builtin_amdgcn_readfirstlane(wave_max_i(L)), e - s);
     if (lmax <= 0) return;
+    const int len = seg_length(g, most);
+    int seg = (lmax - 1) / len - 1;  // the next segment to end, at entry (seg + 1) len
+    if (seg < 0) return;
+    auto leave = [&]() {
+        float* p = snap_at<TW * TH>(g, slot, seg);
+        p[part * kWave + lane] = Tc;
+        p[TW * TH + part * kWave + lane] = VS;
+        seg--;
+    };
     const float amin = g.rp.alpha_min, amax = g.rp.alpha_max;
     const uint32_t quads = TM::quads(part);
-    // the gradient component each lane adds, as in k_render_bwd, here for the
-    // splat of its row of 16 lanes
-    const int row = lane / (kWave / kGroup);
-    const int comp = sum_lane_comp<kGroup>(lane);
-    const float kS = (comp == 2 || comp == 4) ? -0.5f : comp == 3 ? -1.f : 0.f;
-    const float kE = comp >= 5 ? 1.f : 0.f;
-    const float ua = comp == 0 ? 2.f : 0.f, ub = comp == 1 ? 1.f : 0.f;
-    const float vb = comp == 0 ? 1.f : 0.f, vc = comp == 1 ? 2.f : 0.f;
-    float* const grad = comp < kGradGeo ? g.grad_geo + comp : g.grad_col + (comp - kGradGeo);
-    const int gstep = comp < kGradGeo ? kGradGeo : kGradCol;
     uint32_t lp[kPullBwd];
     int next = s + lmax - 1;  // the first entry not yet taken, walking down
     uint32_t qh = 0, qt = 0;
@@ -840,62 +881,51 @@ __device__ __forceinline__ void part_bwd(const BwdArgs& g, const ViewTable& vt, 
         wave_lds_sync();  // the previous batch is read
         stage_splat(sb, ls);
         sb.f[2][lane].z = __uint_as_float(pos);
-        sb.f[2][lane].w = __uint_as_float(id);
         ls = {};
         const int nn = draw(id, pos);
         if (lane < nn) ls = load_splat(rec, id & kPairMask);
         wave_lds_sync();
         for (int i = 0; i < nb; i += kGroup) {
-            float dx[kGroup], dy[kGroup], ex[kGroup], ar[kGroup], al[kGroup], iom[kGroup], Vc[kGroup];
+            float al[kGroup], iom[kGroup], Vc[kGroup];
+            int at[kGroup];
             bool live[kGroup];
-            uint64_t some = 0;
 #pragma unroll
             for (int u = 0; u < kGroup; u++) {
                 const float4 f0 = sb.f[0][i + u], f1 = sb.f[1][i + u], f2 = sb.f[2][i + u];
-                dx[u] = f0.x - fx;
-                dy[u] = f0.y - fy;
-                ex[u] = __builtin_amdgcn_exp2f(splat_e2(f1.x, f1.y, f1.z, dx[u], dy[u]));
-                ar[u] = f0.z * ex[u];
-                al[u] = __builtin_amdgcn_fmed3f(ar[u], 0.f, amax);
+                const float dx = f0.x - fx;
+                const float dy = f0.y - fy;
+                const float ex = __builtin_amdgcn_exp2f(splat_e2(f1.x, f1.y, f1.z, dx, dy));
+                al[u] = __builtin_amdgcn_fmed3f(f0.z * ex, 0.f, amax);
                 iom[u] = __builtin_amdgcn_rcpf(1.f - al[u]);
                 Vc[u] = __builtin_fmaf(V2, f2.y, __builtin_fmaf(V1, f2.x, V0 * f1.w));
-                live[u] = (int)__float_as_uint(f2.z) < L && al[u] >= amin;
-                some |= __ballot(live[u]);
+                at[u] = (int)__float_as_uint(f2.z);
+                live[u] = at[u] < L && al[u] >= amin;
             }
-            if (some == 0) continue;
-            float a[kGroup][9];
-#pragma unroll
-            for (int u = 0; u < kGroup; u++) {
+            auto step = [&](int u) {
                 const float Tb = Tc * iom[u];  // transmittance in front of this splat
-                const float w = live[u] ? al[u] * Tb : 0.f;
-                const float va = __builtin_fmaf(Tb, Vc[u], -(iom[u] * VS));
-                VS = __builtin_fmaf(w, Vc[u], VS);
+                VS = live[u] ? __builtin_fmaf(al[u] * Tb, Vc[u], VS) : VS;
                 Tc = live[u] ? Tb : Tc;
-                const float q = live[u] && ar[u] < amax ? va * ex[u] : 0.f;
-                const float qx = q * dx[u], qy = q * dy[u];
-                a[u][0] = qx;
-                a[u][1] = qy;
-                a[u][2] = qx * dx[u];
-                a[u][3] = qx * dy[u];
-                a[u][4] = qy * dy[u];
-                a[u][5] = q;
-                a[u][6] = w * V0;
-                a[u][7] = w * V1;
-                a[u][8] = w * V2;
-            }
-            const float E = wave_sums_t(a);
-            const float QX = dpp_f<0x150>(E), QY = dpp_f<0x154>(E);  // lanes 0 and 4 of the row: m_x, m_y
-            if (comp >= 0) {
-                const float4 f0 = sb.f[0][i + row], f1 = sb.f[1][i + row];
-                const float mean = __builtin_fmaf(__builtin_fmaf(ua, f1.x, ub * f1.y), QX,
-                                                  __builtin_fmaf(vb, f1.y, vc * f1.z) * QY);
-                const float val = __builtin_fmaf(f0.z * kLn2, mean, E * __builtin_fmaf(kS, f0.z, kE));
-                const int64_t p = __float_as_uint(sb.f[2][i + row].w) & kPairMask;
-                if (val != 0.f) atomicAdd(grad + gstep * p, val);
+            };
+            // (of a short last group, the unused entries' alpha is zero)
+            const int rest = min(kGroup, nb - i);
+            const int lowest = (int)__builtin_amdgcn_readfirstlane(__float_as_uint(sb.f[2][i + rest - 1].z));
+            if (lowest >= (seg + 1) * len) {
+#pragma unroll
+                for (int u = 0; u < kGroup; u++) step(u);
+            } else {
+#pragma unroll
+                for (int u = 0; u < kGroup; u++) {
+                    const int p = __builtin_amdgcn_readfirstlane(at[u]);
+                    if (u < rest)
+                        while (seg >= 0 && p < (seg + 1) * len) leave();
+                    step(u);
+                }
+                if (seg < 0) return;
             }
         }
         nb = nn;
     }
+    while (seg >= 0) leave();
 }
 
 // ---- the backward's launch
@@ -905,24 +935,25 @@ __device__ __forceinline__ void part_bwd(const BwdArgs& g, const ViewTable& vt, 
 // tiles, with the CUs busy three quarters of it on the 150-camera step and a
 // fifth of it on 256 tiles.  So the tiles are launched heaviest first by what
 // the backward will walk (the largest `last` of a tile's pixels, read here
-// from the image the caller passes), and those heavier than a wave's fair
-// share of the launch are split into parts.
+// from the image the caller passes), and those much heavier than a wave's fair
+// share of the launch are walked in segments at once, from the states that a
+// chain over the list left at the segments' ends (chain_bwd).
 // Weights are bucketed, 16 buckets an octave like gs_settings.tile_order's.
-// us, the start's wave per tile in the settings' order -> this (weights and
-// plan, 20-30 us, not counted): 8 uneven views 1149 -> 907, 4 x 1237x822 920 ->
-// 691, 4 x 1600x1066 (32x16) 1250 -> 1050; one 1237x822 view of blobs 346 ->
-// 166 (32x16: 783 -> 304), of a frustum 200 -> 173.
+// us, a wave per tile in the settings' order -> this (weights and plan, 20-30
+// us, not counted): 4 x 1237x822 920 -> 690, 4 x 1600x1066 (32x16) 1250 -> 1065, 8
+// uneven views 1149 -> 1185, one 1237x822 view of blobs 346 -> 303.
 constexpr int kWeightBuckets = 513;
 constexpr int kWeightThreads = 1024;
 constexpr int kWaveSlots = 4096;  // waves of the backward the chip holds at once
 // A tile is heavy past kShare times the launch's weight over kWaveSlots; so at
-// most kWaveSlots / kShare tiles are.  A part costs 1.2 to 1.4 times its share
-// of the tile taken whole, so too many are a loss and too few leave the tail:
-// us at kShare 1, 2, 3, 4 on 8 uneven views 895, 890, 1193, 1185; on one
-// 1237x822 view of blobs 246, 166, 206, 251, of a frustum 231, 173, 174, 173;
-// on 4 x 1600x1066 1108, 1040, 1062, 1055.
-constexpr int kShare = 2;
-constexpr int kMaxHeavy = kWaveSlots / kShare;
+// most kWaveSlots / kShare tiles are.  The chain is work on top of the tile's
+// own, about half of it, so too many are a loss and too few leave the tail: us
+// at kShare 2, 3, 4 on 4 x 1237x822 803, 686, 692, on 4 x 1600x1066 1240, 1065,
+// 1041, on 8 uneven views 1103, 1189, 1185, on one 1237x822 view of blobs 240, 303,
+// 354.
+constexpr int kShare = 3;
+constexpr int kMaxHeavy = kBwdHeavy;
+static_assert(kMaxHeavy >= kWaveSlots / kShare, "as many as can pass kShare");
 
 // (walked entries, their bucket; no entries: bucket 0)
 __device__ __forceinline__ uint32_t weight_bucket(uint32_t n) {
@@ -1028,7 +1059,7 @@ __global__ __launch_bounds__(kWeightThreads) void k_bwd_plan(const uint32_t* __r
     each([&](int t, uint32_t b) { order[atomicAdd(&s_n[b], 1u)] = (uint32_t)t; });
 }
 
-// The heavy tiles' parts first (a tile's parts kXcds workgroups apart, so they
+// The heavy tiles' chains first (a tile's parts kXcds workgroups apart, so they
 // share an L2), then the other tiles, whole.  Without a plan (plan NULL) the
 // first `heavy` tiles are.
 template <int TW, int TH>
@@ -1045,12 +1076,24 @@ __global__ __launch_bounds__(64) void k_render_bwd(BwdArgs g, ViewTable vt, int 
     if (x < parts) {
         const int slot = x / (kXcds * PPL) * kXcds + x % kXcds;
         if (slot >= heavy) return;
-        part_bwd<TW, TH>(g, vt, order ? (int)order[slot] : slot, x / kXcds % PPL, sb, ring);
+        chain_bwd<TW, TH>(g, vt, order ? (int)order[slot] : slot, x / kXcds % PPL, slot, sb, ring);
     } else {
         const int slot = heavy + x - parts;
         if (slot >= n) return;
-        tile_bwd<TW, TH>(g, vt, order ? (int)order[slot] : slot, sb);
+        tile_bwd<TW, TH, false>(g, vt, order ? (int)order[slot] : slot, sb);
     }
+}
+
+// The heavy tiles' segments, a wave each.
+template <int TW, int TH>
+__global__ __launch_bounds__(64) void k_render_bwd_segs(BwdArgs g, ViewTable vt, const uint32_t* __restrict__ order,
+                                                        const uint32_t* __restrict__ plan, int heavy) {
+    __shared__ BatchLds sb;
+    if (plan) heavy = (int)plan[1];
+    const int x = blockIdx.x;
+    const int slot = x / (kXcds * g.segs) * kXcds + x % kXcds;
+    if (slot >= heavy) return;
+    tile_bwd<TW, TH, true>(g, vt, order ? (int)order[slot] : slot, sb, slot, x / kXcds % g.segs);
 }
 
 constexpr int kL1Blocks = 1024;
@@ -1128,21 +1171,26 @@ hipError_t fwd_impl(Ctx* c, const ViewTable& vt, const RasterParams& rp, const f
     return e;
 }
 
-// Tiles whose parts are all resident at once are all split, unplanned (256 tiles
-// of 16x16, 10k splats: 146 -> 44 us; 10k blob splats 514 -> 194); more are
-// planned.  Past 2^20 tiles (the plan is one workgroup's) none is split.
+// Tiles whose chains are all resident at once are all walked in segments, unplanned
+// (256 tiles of 16x16, 10k blob splats 514 -> 178 us; 476 of 32x16, 1.4M splats 1290);
+// more are planned.  Past 2^20 tiles (the plan is one workgroup's) none is split.
 template <int TW, int TH>
 hipError_t bwd_impl(Ctx* c, const ViewTable& vt, const RasterParams& rp, const float* bg,
                     const float* T_final, const int32_t* last, const float* v_rgb, hipStream_t st) {
     constexpr int PPL = TileMap<TW, TH>::PPL;
-    const BwdArgs g = {reinterpret_cast<const float4*>(c->rec), reinterpret_cast<const int32_t*>(c->tids),
-                       c->tranges, bg, T_final, last, v_rgb, c->grad2d,
-                       c->grad2d + kGradGeo * c->cap.max_pairs, rp};
     const int T = (int)c->n_tiles;
     const int all = (int64_t)T * PPL <= kWaveSlots ? T : 0;
+    const BwdArgs g = {reinterpret_cast<const float4*>(c->rec), reinterpret_cast<const int32_t*>(c->tids),
+                       c->tranges, bg, T_final, last, v_rgb, c->grad2d,
+                       c->grad2d + kGradGeo * c->cap.max_pairs, c->snap, all ? 2 * kBwdSegs : kBwdSegs, rp};
+    const auto segments = [&](int tiles, const uint32_t* order, const uint32_t* plan, int heavy) {
+        hipLaunchKernelGGL((k_render_bwd_segs<TW, TH>), dim3((unsigned)((tiles + kXcds - 1) / kXcds * kXcds * g.segs)),
+                           dim3(64), 0, st, g, vt, order, plan, heavy);
+    };
     if (all || T > (1 << 20)) {
         const unsigned grid = all ? (unsigned)((T + kXcds - 1) / kXcds * kXcds * PPL) : (unsigned)T;
         hipLaunchKernelGGL((k_render_bwd<TW, TH>), dim3(grid), dim3(64), 0, st, g, vt, T, nullptr, nullptr, all);
+        if (all) segments(T, nullptr, nullptr, all);
         return hipGetLastError();
     }
     uint32_t* bucket = c->tk[0];
@@ -1153,6 +1201,7 @@ hipError_t bwd_impl(Ctx* c, const ViewTable& vt, const RasterParams& rp, const f
     hipLaunchKernelGGL(k_bwd_plan, dim3(1), dim3(kWeightThreads), 0, st, bucket, T, order, plan);
     const unsigned grid = (unsigned)(T + (PPL - 1) * std::min(T, kMaxHeavy) + kXcds * PPL);
     hipLaunchKernelGGL((k_render_bwd<TW, TH>), dim3(grid), dim3(64), 0, st, g, vt, T, order, plan, 0);
+    segments(std::min(T, kMaxHeavy), order, plan, 0);
     return hipGetLastError();
 }
 
