@@ -692,7 +692,7 @@ def _bench_line(raw, name):
 CALL_KERNELS = {
     "project": lambda k: k.startswith("k_project_fwd<"),
     "render_fwd": lambda k: k.startswith("k_render_fwd_part<"),
-    "raster_bwd": lambda k: k.startswith("k_render_bwd<"),
+    "raster_bwd": lambda k: k.startswith("k_render_bwd"),
     "photo": lambda k: k == "k_photo",
     "project_bwd_adam": lambda k: k in ("k_project_bwd_color<3, true>", "k_project_bwd_geom<true>"),
     "track": lambda k: k.split("<")[0] in ("k_track", "k_track_points", "k_track_pm", "k_track_pm_reduce"),

@@ -5,7 +5,7 @@
 // fixed tile quadrants; every list entry carries the quadrants its splat
 // reaches.  The forward gives each slot (a part of the tile) a wave, one pixel a
 // lane; the backward gives a wave a whole tile, PPL pixels a lane, or for the
-// heaviest tiles a part.  Lists are consumed in batches of 64: each lane loads
+// heaviest tiles a segment of its list.  Lists are consumed in batches of 64: each lane loads
 // one splat record (a gather of 40 B) and stages it in the wave's own LDS
 // region; the wave then walks the batch reading each splat's parameters with
 // broadcast LDS loads (one address for all lanes), synchronising only with
