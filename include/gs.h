@@ -200,8 +200,9 @@ const char* gs_strerror(gs_status s);
 void gs_default_settings(gs_settings* s);
 
 /* Create a context: allocates the whole workspace once (device memory of about
- * 48+36+24 B per pair + 36 B per list entry + 40 B per tile, and 12 KB per
- * camera up to GS_TRACK_PM_MAX_CAMS).  *out is NULL on failure. */
+ * 48+36+24 B per pair + 36 B per list entry + 40 B per tile, 6 KB per
+ * camera up to GS_TRACK_PM_MAX_CAMS, and 29 KB per tile but at most 39 MB for
+ * the raster backward's heavy tiles).  *out is NULL on failure. */
 gs_status gs_ctx_create(gs_ctx** out, const gs_capacity* cap);
 gs_status gs_ctx_destroy(gs_ctx* ctx);
 /* Synchronise the device and read the status word. */
