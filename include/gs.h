@@ -117,9 +117,8 @@ typedef struct {
     float alpha_max;          /* 0.99 */
     float t_min;              /* 1e-4 */
     int32_t grad_accumulate;  /* 0: gs_render_bwd overwrites Gaussian grads; 1: adds */
-    int32_t tile_order;       /* launch order of the forward (the backward orders its tiles
-                                 by what it will walk).  0: natural tile order; 1: the
-                                 tiles heaviest first: by decreasing bucket of the
+    int32_t tile_order;       /* 0: natural tile order; 1: launch the raster kernels on
+                                 the tiles heaviest first: by decreasing bucket of the
                                  list length, 16 buckets per octave (bucket of n > 0:
                                  1 + 16 floor(log2 n) + the 4 bits after n's leading
                                  bit; 0 for an empty list), any order inside a bucket;
@@ -127,7 +126,8 @@ typedef struct {
                                  consecutive workgroups of one XCD (workgroups are dealt
                                  round-robin over the 8 XCDs), so neighbouring tiles read
                                  their shared splats through one L2.  The image does not
-                                 depend on the order */
+                                 depend on the order; gradients do in their rounding (a
+                                 splat's tiles add to them as they run) */
     int32_t eval_stats;       /* 0; 1: gs_render_fwd also counts per tile the contributing
                                  pairs, list entries read and (pixel, splat) evaluations
                                  (gs_ctx_tile_stats), a slower variant */
@@ -200,9 +200,8 @@ const char* gs_strerror(gs_status s);
 void gs_default_settings(gs_settings* s);
 
 /* Create a context: allocates the whole workspace once (device memory of about
- * 48+36+24 B per pair + 36 B per list entry + 40 B per tile, 6 KB per
- * camera up to GS_TRACK_PM_MAX_CAMS, and 29 KB per tile but at most 39 MB for
- * the raster backward's heavy tiles).  *out is NULL on failure. */
+ * 48+36+24 B per pair + 36 B per list entry + 40 B per tile, and 6 KB per
+ * camera up to GS_TRACK_PM_MAX_CAMS).  *out is NULL on failure. */
 gs_status gs_ctx_create(gs_ctx** out, const gs_capacity* cap);
 gs_status gs_ctx_destroy(gs_ctx* ctx);
 /* Synchronise the device and read the status word. */

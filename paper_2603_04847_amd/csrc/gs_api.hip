@@ -205,7 +205,6 @@ gs_status gs_ctx_create(gs_ctx** out, const gs_capacity* cap) {
     const int64_t scanmax = std::max<int64_t>(std::max<int64_t>((int64_t)hw, 16 * (c.nchunks + 1)), sortmax);
     A(dalloc(&c.scan_scratch, gs::scan_scratch_words(scanmax)));
     c.scan_max = scanmax;
-    A(dalloc(&c.snap, gs::snap_floats(T)));
     A(dalloc(&c.scalars, 16));
     const int nv = cap->max_views;
     const int nc = cap->max_cams > 0 ? cap->max_cams : 1;
@@ -243,7 +242,7 @@ gs_status gs_ctx_destroy(gs_ctx* h) {
     void* ptrs[] = {c.rec, c.grad2d, c.vmu_dir, c.cnt, c.off, c.pk[0], c.pk[1], c.pv[0], c.pv[1],
                     c.ik[0], c.ik[1], c.iv[0], c.iv[1], c.im[0], c.im[1], c.tcnt, c.ccnt, c.cbase, c.bpre, c.bplace, c.tbase, c.tranges, c.tids,
                     c.ranges, c.tile_order, c.tk[0], c.tk[1], c.tile_contrib, c.tile_entries, c.tile_evals, c.hist,
-                    c.scan_scratch, c.snap, c.scalars, c.twist_render, c.twist_track, c.track_part,
+                    c.scan_scratch, c.scalars, c.twist_render, c.twist_track, c.track_part,
                     c.track_loss_part, c.loss_acc, c.aux, c.diag};
     hipDeviceSynchronize();
     for (void* p : ptrs)

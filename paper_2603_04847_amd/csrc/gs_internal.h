@@ -80,75 +80,43 @@ __device__ __forceinline__ float wave_sum(float v) {
     return bcast(v, 63);
 }
 
-// The two halves of a pair of registers exchanged and added: the lower half of
-// the lanes (or, for 16, the even rows) gets a's sum over lanes l and l ^ 32 (l
-// ^ 16), the upper half (the odd rows) b's.
-__device__ __forceinline__ float fold32(float a, float b) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    const unsigned lo = r[0], hi = r[1];
-    return __uint_as_float(lo) + __uint_as_float(hi);
-}
-__device__ __forceinline__ float fold16(float a, float b) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    const unsigned lo = r[0], hi = r[1];
-    return __uint_as_float(lo) + __uint_as_float(hi);
-}
-
-// Nine values summed over each row of 16 lanes: the first eight halved three
-// times by exchanging with the quad partner lane^1 and lane^2 (keeping the half
-// picked by that lane bit) and with the lane four places round the row, then
-// summed over the rest of it: e in every lane is the total of value
-// sum8_index(lane & 7).  The ninth, z, is summed alone.
-__device__ __forceinline__ void row_sum9_t(const float (&r)[9], float& e, float& z) {
+// Wave totals of nine per-lane values in about a third of the instructions of
+// nine separate sums.  The first eight are halved three times by exchanging
+// with the quad partner lane^1 and lane^2 (keeping the half picked by that lane
+// bit) and with the lane four places round the 16-lane row; the ninth is summed
+// over its quads alone; both are then summed over the row (rotate by 8).  The
+// last two steps need no LDS: v_permlane16_swap swaps the odd rows of one
+// register with the even rows of another (rows 0 and 2 then hold the eight,
+// rows 1 and 3 the ninth), and v_permlane32_swap the upper half of one with
+// the lower half of another.  On return lanes 0-15 and 32-47 hold the total of
+// value sum8_index(lane & 7), lanes 16-31 and 48-63 the total of a8.
+__device__ __forceinline__ float wave_sum9_t(float a0, float a1, float a2, float a3, float a4, float a5,
+                                             float a6, float a7, float a8) {
     const int lane = __lane_id();
     const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
-    const float c0 = (b0 ? r[4] : r[0]) + dpp_f<0xB1>(b0 ? r[0] : r[4]);
-    const float c1 = (b0 ? r[5] : r[1]) + dpp_f<0xB1>(b0 ? r[1] : r[5]);
-    const float c2 = (b0 ? r[6] : r[2]) + dpp_f<0xB1>(b0 ? r[2] : r[6]);
-    const float c3 = (b0 ? r[7] : r[3]) + dpp_f<0xB1>(b0 ? r[3] : r[7]);
+    const float c0 = (b0 ? a4 : a0) + dpp_f<0xB1>(b0 ? a0 : a4);
+    const float c1 = (b0 ? a5 : a1) + dpp_f<0xB1>(b0 ? a1 : a5);
+    const float c2 = (b0 ? a6 : a2) + dpp_f<0xB1>(b0 ? a2 : a6);
+    const float c3 = (b0 ? a7 : a3) + dpp_f<0xB1>(b0 ? a3 : a7);
     const float d0 = (b1 ? c2 : c0) + dpp_f<0x4E>(b1 ? c0 : c2);
     const float d1 = (b1 ? c3 : c1) + dpp_f<0x4E>(b1 ? c1 : c3);
-    e = (b2 ? d1 : d0) + dpp_f<0x124>(b2 ? d0 : d1);  // row_ror:4
-    e += dpp_f<0x128>(e);                               // row_ror:8
-    z = r[8] + dpp_f<0xB1>(r[8]);
+    float e = (b2 ? d1 : d0) + dpp_f<0x124>(b2 ? d0 : d1);  // row_ror:4
+    e += dpp_f<0x128>(e);                                     // row_ror:8
+    float z = a8 + dpp_f<0xB1>(a8);
     z += dpp_f<0x4E>(z);
     z += dpp_f<0x124>(z);
     z += dpp_f<0x128>(z);
-}
-
-// Wave totals of nine values for each of two splats: 58 instructions, the rows
-// first, then the odd rows added to the even, then the halves.  Lanes 0-7 of
-// half u of the wave hold the first eight of splat u (sum8_index), lane 16 of it
-// the ninth.
-__device__ __forceinline__ float wave_sums_t(const float (&a)[2][9]) {
-    float e0, z0, e1, z1;
-    row_sum9_t(a[0], e0, z0);
-    row_sum9_t(a[1], e1, z1);
-    return fold32(fold16(e0, z0), fold16(e1, z1));
-}
-
-// The same for four splats, the lane swaps first, since they halve two
-// registers in two instructions where a DPP exchange takes three: 80
-// instructions.  Lanes 0-7 of row u of 16 lanes hold the first eight of splat
-// u, lane 8 of it the ninth.
-__device__ __forceinline__ float wave_sums_t(const float (&a)[4][9]) {
-    float r[9], e, z;
-#pragma unroll
-    for (int c = 0; c < 9; c++) r[c] = fold16(fold32(a[0][c], a[2][c]), fold32(a[1][c], a[3][c]));
-    row_sum9_t(r, e, z);
-    return (__lane_id() & 8) ? z : e;
+    // (the pair's elements are copied out before any bit cast)
+    const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(e), __float_as_uint(z), false, false);
+    const unsigned s0 = r16[0], s1 = r16[1];
+    const float f = __uint_as_float(s0) + __uint_as_float(s1);
+    const auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(f), __float_as_uint(f), false, false);
+    const unsigned t0 = r32[0], t1 = r32[1];
+    return __uint_as_float(t0) + __uint_as_float(t1);
 }
 
 __device__ __forceinline__ int sum8_index(int lane) {
     return ((lane & 1) << 2) | (lane & 2) | ((lane >> 2) & 1);
-}
-
-// which of the nine values a lane holds after wave_sums_t over U splats (-1:
-// a copy)
-template <int U>
-__device__ __forceinline__ int sum_lane_comp(int lane) {
-    const int l = lane % (kWave / U);
-    return l < 8 ? sum8_index(l) : l == (U == 4 ? 8 : 16) ? 8 : -1;
 }
 
 __device__ __forceinline__ int wave_max_i(int v) {
@@ -627,18 +595,6 @@ hipError_t launch_flush_twist_rows(double* acc, float* out, const ViewTable& vt,
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t st);
 
 // The context (workspace), shared by the launchers.
-constexpr int kScalarPlan = 8;
-// The raster backward: the segments of a heavy tile at most (twice as many where
-// every tile is taken so: up to 2^18 pixels' worth of them), the heavy tiles at
-// most, and the floats of the pixel states between the segments.
-constexpr int kBwdSegs = 8;
-constexpr int kBwdHeavy = 1366;
-inline size_t snap_floats(int64_t max_tiles) {
-    const int64_t heavy = (max_tiles < kBwdHeavy ? max_tiles : kBwdHeavy) * (kBwdSegs - 1) * 2 * 512;
-    const int64_t px = max_tiles * 512 < (1 << 18) ? max_tiles * 512 : 1 << 18;
-    const int64_t all = px * (2 * kBwdSegs - 1) * 2;
-    return (size_t)(heavy > all ? heavy : all);
-}
 struct Ctx {
     gs_capacity cap;
     int device;
@@ -671,8 +627,7 @@ struct Ctx {
     int32_t* tile_evals;   // [max_tiles] (pixel, entry) evaluations up to the last contributors
     uint32_t* hist;        // radix histograms
     uint32_t* scan_scratch;
-    float* snap;           // [snap_floats] pixel states between the backward's segments
-    uint32_t* scalars;     // small device counters (from kScalarPlan: the raster backward's plan)
+    uint32_t* scalars;     // small device counters
     double* twist_render;  // [max_views][6]
     double* twist_track;   // [max_cams][6]
     float* track_part;     // [kTrackPmBlocks][6 pm_cams] per-workgroup twist sums (point-major pass)

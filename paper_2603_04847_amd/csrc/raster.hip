@@ -4,16 +4,15 @@
 // A tile of TW x TH pixels is PPL = TW*TH/64 slots of 64 pixels, each slot in
 // fixed tile quadrants; every list entry carries the quadrants its splat
 // reaches.  The forward gives each slot (a part of the tile) a wave, one pixel a
-// lane; the backward gives a wave a whole tile, PPL pixels a lane, or for the
-// heaviest tiles a segment of its list.  Lists are consumed in batches of 64: each lane loads
-// one splat record (a gather of 40 B) and stages it in the wave's own LDS
-// region; the wave then walks the batch reading each splat's parameters with
-// broadcast LDS loads (one address for all lanes), synchronising only with
-// itself, while the next batch's records and the entries after it are in
-// flight.  The backward walks the lists back to front from each pixel's last
-// contributor, recovering the transmittance by division, and sums the splats'
-// nine 2D gradients over the whole wave (DPP and lane-swap steps) before one
-// lane per component issues the global atomic.
+// lane; the backward gives a wave a whole tile, PPL pixels a lane.  Lists are
+// consumed in batches of 64: each lane loads one splat record (a gather of 40 B)
+// and stages it in the wave's own LDS region; the wave then walks the batch
+// reading each splat's parameters with broadcast LDS loads (one address for all
+// lanes), synchronising only with itself, while the next batch's records and
+// the entries after it are in flight.  The backward walks the lists back to
+// front from each pixel's last contributor, recovering the transmittance by
+// division, and sums each splat's nine 2D gradients over the whole wave (DPP and
+// lane-swap steps) before one lane per component issues the global atomic.
 #include <algorithm>
 
 #include "gs_internal.h"
@@ -339,7 +338,7 @@ __global__ __launch_bounds__(64) void k_render_fwd_stats(const float4* __restric
             }
         }
     }
-    // workload statistics of the tile : contributing
+    // workload statistics of the tile: contributing
     // (pixel, splat) pairs, list entries read, and (pixel, entry) evaluations
     // up to each pixel's last contributor over the entries covering its quadrant
     int nev = 0;
@@ -371,42 +370,33 @@ __global__ __launch_bounds__(64) void k_render_fwd_stats(const float4* __restric
     }
 }
 
-// What the raster backward reads and writes.
-struct BwdArgs {
-    const float4* rec;
-    const int32_t* ids;
-    const int32_t* ranges;
-    const float* bg;
-    const float* T_final;
-    const int32_t* last;
-    const float* v_rgb;
-    float* grad_geo;
-    float* grad_col;
-    float* snap;  // pixel states at the segments' ends (see chain_bwd)
-    int segs;     // segments of a heavy tile at most
-    RasterParams rp;
-};
-
-// A heavy tile's list is walked in at most g.segs segments of whole batches.
-__device__ __forceinline__ int seg_length(const BwdArgs& g, int lmax) {
-    return ((lmax + g.segs - 1) / g.segs + kWave - 1) / kWave * kWave;
-}
-// the states at the end of segment `seg` of the heavy tile in slot `slot`: [2][pixels]
-template <int PIXELS>
-__device__ __forceinline__ float* snap_at(const BwdArgs& g, int slot, int seg) {
-    return g.snap + ((int64_t)slot * (g.segs - 1) + seg) * (2 * PIXELS);
-}
-
-// Tile t by one wave: all of it, or (SEG) segment `seg` of the heavy tile in
-// slot `slot`, whose pixels start from the states that the chain left.
-template <int TW, int TH, bool SEG>
-__device__ __forceinline__ void tile_bwd(const BwdArgs& g, const ViewTable& vt, int t, BatchLds& sb, int slot = 0,
-                                         int seg = 0) {
+// The backward: a wave per tile, in the settings' launch order.  Bound by its
+// arithmetic, and by the last heavy tiles of a launch.
+//
+// A splat's tiles add their sums by float atomics, so the order the tiles run in
+// decides how its gradient rounds; and a needle-like splat's conic gradients
+// cancel when the projection backward turns them into its scales and rotation,
+// which puts single entries of those up to 2e-3 of the gradient's rms apart
+// between two orders (4 x 1600x1066, 5M splats, where two runs in one order
+// are 5e-4 apart).  So the tiles run neither heaviest first by what they walk nor
+// cut into waves that walk a list's segments at once, though both are faster:
+// us for this, and for those, on 4 x 1237x822 890 and 680, on 4 x 1600x1066 1665
+// and 1080, on one 256x256 view 146 and 91; on 8 uneven views 1120 and 1145.
+template <int TW, int TH>
+__global__ __launch_bounds__(64) void k_render_bwd(const float4* __restrict__ rec,
+                                                   const int32_t* __restrict__ ids,
+                                                   const int32_t* __restrict__ ranges,
+                                                   const uint32_t* __restrict__ order, ViewTable vt,
+                                                   RasterParams rp, const float* __restrict__ bg,
+                                                   const float* __restrict__ T_final,
+                                                   const int32_t* __restrict__ last_in,
+                                                   const float* __restrict__ v_rgb,
+                                                   float* __restrict__ grad_geo,
+                                                   float* __restrict__ grad_col, int mode) {
     using TM = TileMap<TW, TH>;
     constexpr int PPL = TM::PPL;
-    const float4* __restrict__ rec = g.rec;
-    const int32_t* __restrict__ ids = g.ids;
-    const float* bg = g.bg;
+    int t;
+    if (!block_tile(blockIdx.x, order, mode, vt, t)) return;
     const int v = tile_view(vt, t);
     const int lt = t - vt.tile_off[v];
     const int gx = vt.gx[v], W = vt.W[v], H = vt.H[v];
@@ -428,11 +418,11 @@ __device__ __forceinline__ void tile_bwd(const BwdArgs& g, const ViewTable& vt, 
         V0[k] = V1[k] = V2[k] = 0.f;
         if (px < W && py < H) {
             const int64_t pix = (int64_t)vt.pix_off[v] + (int64_t)py * W + px;
-            L[k] = g.last[pix];
-            Tc[k] = g.T_final[pix];
-            V0[k] = g.v_rgb[3 * pix];
-            V1[k] = g.v_rgb[3 * pix + 1];
-            V2[k] = g.v_rgb[3 * pix + 2];
+            L[k] = last_in[pix];
+            Tc[k] = T_final[pix];
+            V0[k] = v_rgb[3 * pix];
+            V1[k] = v_rgb[3 * pix + 1];
+            V2[k] = v_rgb[3 * pix + 2];
         }
         // VS = dL/dC . S, S = sum over later splats of colour alpha T, plus
         // T_final bg (the background term seeds it)
@@ -446,130 +436,107 @@ __device__ __forceinline__ void tile_bwd(const BwdArgs& g, const ViewTable& vt, 
 #pragma unroll
     for (int k = 0; k < PPL; k++) Lk[k] = __builtin_amdgcn_readfirstlane(wave_max_i(L[k]));
     lmax = __builtin_amdgcn_readfirstlane(wave_max_i(lmax));
-    const int s = g.ranges[2 * t], e = g.ranges[2 * t + 1];
+    const int s = ranges[2 * t], e = ranges[2 * t + 1];
     lmax = min(lmax, e - s);  // a pixel's last contributor lies inside its tile's list
     if (lmax <= 0) return;
-    const float amin = g.rp.alpha_min, amax = g.rp.alpha_max;
-    int low = s, top = s + lmax;  // entries [s, top) can matter; this wave's are [low, top)
-    if (SEG) {
-        const int len = seg_length(g, lmax), end = (seg + 1) * len;
-        if (seg * len >= lmax) return;
-        low = s + seg * len;
-        top = min(top, s + end);
-        const float* snap = snap_at<TW * TH>(g, slot, seg);
-#pragma unroll
-        for (int k = 0; k < PPL; k++)
-            if (end < min(Lk[k], e - s)) {  // wave-uniform: the slot's pixels reach past the end
-                Tc[k] = snap[k * kWave + lane];
-                VS[k] = snap[TW * TH + k * kWave + lane];
-            }
-    }
-    // The gradient component this lane adds after the wave sums E of two splats
-    // (the first in lanes 0-31, the second in 32-63; see wave_sums_t): 0 mean.x,
-    // 1 mean.y, 2 A, 3 B, 4 C, 5 opacity, 6 r, 7 g, 8 b, -1 none.
+    const float amin = rp.alpha_min, amax = rp.alpha_max;
+    const int top = s + lmax;  // entries [s, top) can matter
+    // The gradient component this lane adds after each splat's wave sum E
+    // (lanes 0-7 hold value sum8_index(lane), lane 16 the blue sum; the rest
+    // add none): 0 mean.x, 1 mean.y, 2 A, 3 B, 4 C, 5 opacity, 6 r, 7 g, 8 b.
     // It is E (kS o + kE) + o ln2 ((ua a + ub b) QX + (vb b + vc c) QY) with
     // QX, QY the first two moments, so every lane runs the same instructions.
-    const int comp = sum_lane_comp<2>(lane);
-    float* const grad = comp < kGradGeo ? g.grad_geo + comp : g.grad_col + (comp - kGradGeo);
-    const int gstep = comp < kGradGeo ? kGradGeo : kGradCol;
+    const int comp = lane < 8 ? sum8_index(lane) : lane == 16 ? 8 : -1;
     const float kS = (comp == 2 || comp == 4) ? -0.5f : comp == 3 ? -1.f : 0.f;
     const float kE = comp >= 5 ? 1.f : 0.f;
     const float ua = comp == 0 ? 2.f : 0.f, ub = comp == 1 ? 1.f : 0.f;
     const float vb = comp == 0 ? 1.f : 0.f, vc = comp == 1 ? 2.f : 0.f;
-    int b = low + ((top - low - 1) / kWave) * kWave;
+    __shared__ BatchLds sb;
+    int b = s + ((lmax - 1) / kWave) * kWave;
     // the same two-deep pipeline as the forward, walking down: the batches
     // after the first (partial) one are full
     uint32_t id_cur = batch_ids(ids, b, s, top);
     uint32_t id_nxt = batch_ids(ids, b - kWave, s, top);
     LaneSplat ls_cur = {};
     if (lane < top - b) ls_cur = load_splat(rec, id_cur & kPairMask);
-    for (; b >= low; b -= kWave) {
+    // per-lane sums over the lane's pixels for the current splat: colour
+    // weights, q = dL/dalpha e^-sigma (zero where alpha is clamped), and the
+    // moments q dx, q dy, q dx^2, q dx dy, q dy^2; the exponent's gradient is
+    // -o q, so the mean and conic gradients follow from these after the wave
+    // sum.  They are zero at every splat's start: a splat nobody contributes
+    // to leaves them untouched, one that is summed clears them afterwards.
+    float g_r = 0.f, g_g = 0.f, g_b = 0.f, g_o = 0.f;
+    float m_x = 0.f, m_y = 0.f, m_xx = 0.f, m_xy = 0.f, m_yy = 0.f;
+    bool any = false;
+    for (; b >= s; b -= kWave) {
         const uint32_t id = id_cur;
         const int nb = min(kWave, top - b);
         wave_lds_sync();  // the previous batch is read
         stage_splat(sb, ls_cur);
         ls_cur = {};
-        if (b - kWave >= low) ls_cur = load_splat(rec, id_nxt & kPairMask);
+        if (b - kWave >= s) ls_cur = load_splat(rec, id_nxt & kPairMask);
         id_cur = id_nxt;
         id_nxt = batch_ids(ids, b - 2 * kWave, s, top);
         wave_lds_sync();
-        // Two splats at a time: their nine sums each are then taken over the
-        // wave in one butterfly and added by one atomic instruction, which
-        // costs 35 instructions a splat where one by one it was 51.
-        for (int i = nb - 1; i >= 0; i -= 2) {
-            // per-lane sums over the lane's pixels: q dx, q dy, q dx^2, q dx dy,
-            // q dy^2 and q, q = dL/dalpha e^-sigma (zero where alpha is
-            // clamped), then the colour weights; the exponent's gradient is
-            // -o q, so the mean and conic gradients follow from these after the
-            // wave sum
-            float a[2][9];
-            float4 f0[2], f1[2];
-            bool any = false;
+        for (int i = nb - 1; i >= 0; i--) {
+            const uint32_t idb = (uint32_t)bcast((int)id, i);
+            const uint32_t m = idb >> kPairBits;
+            const float4 f0 = sb.f[0][i], f1 = sb.f[1][i], f2 = sb.f[2][i];
+            const float mx = f0.x, my = f0.y, o = f0.z;
+            const float qa = f1.x, qb = f1.y, qc = f1.z, cr = f1.w, cg = f2.x, cb = f2.y;
+            const int pos = b + i - s;
 #pragma unroll
-            for (int u = 0; u < 2; u++) {
-#pragma unroll
-                for (int c = 0; c < 9; c++) a[u][c] = 0.f;
-                const int j = max(i - u, 0);
-                const uint32_t m = i >= u ? (uint32_t)bcast((int)id, j) >> kPairBits : 0u;
-                f0[u] = sb.f[0][j];
-                f1[u] = sb.f[1][j];
-                const float4 f2 = sb.f[2][j];
-                const float mx = f0[u].x, my = f0[u].y, o = f0[u].z;
-                const float qa = f1[u].x, qb = f1[u].y, qc = f1[u].z, cr = f1[u].w, cg = f2.x, cb = f2.y;
-                const int pos = b + j - s;
-#pragma unroll
-                for (int k = 0; k < PPL; k++) {
-                    if (!(m & TM::quads(k)) || pos >= Lk[k]) continue;  // wave-uniform
-                    const float dx = mx - fx[k];
-                    const float dy = my - fy[k];
-                    const float e2 = splat_e2(qa, qb, qc, dx, dy);
-                    const float ex = __builtin_amdgcn_exp2f(e2);
-                    const float araw = o * ex;
-                    const float alpha = __builtin_amdgcn_fmed3f(araw, 0.f, amax);
-                    // same decisions as the forward: before the pixel's last
-                    // contributor and above the alpha gate
-                    const bool live = pos < L[k] && alpha >= amin;
-                    if (live) {
-                        any = true;
-                        const float iom = __builtin_amdgcn_rcpf(1.f - alpha);
-                        const float Tb = Tc[k] * iom;  // transmittance in front of this splat
-                        const float w = alpha * Tb;
-                        a[u][6] = __builtin_fmaf(w, V0[k], a[u][6]);
-                        a[u][7] = __builtin_fmaf(w, V1[k], a[u][7]);
-                        a[u][8] = __builtin_fmaf(w, V2[k], a[u][8]);
-                        const float Vc = __builtin_fmaf(V2[k], cb, __builtin_fmaf(V1[k], cg, V0[k] * cr));
-                        // dL/dalpha = T (dL/dC . c) - (dL/dC . S) / (1 - alpha)
-                        const float va = __builtin_fmaf(Tb, Vc, -(iom * VS[k]));
-                        VS[k] = __builtin_fmaf(w, Vc, VS[k]);
-                        Tc[k] = Tb;
-                        const float q = araw < amax ? va * ex : 0.f;  // clamped alpha passes no gradient
-                        a[u][5] += q;
-                        const float qx = q * dx, qy = q * dy;
-                        a[u][0] += qx;
-                        a[u][1] += qy;
-                        a[u][2] = __builtin_fmaf(qx, dx, a[u][2]);
-                        a[u][3] = __builtin_fmaf(qx, dy, a[u][3]);
-                        a[u][4] = __builtin_fmaf(qy, dy, a[u][4]);
-                    }
+            for (int k = 0; k < PPL; k++) {
+                if (!(m & TM::quads(k)) || pos >= Lk[k]) continue;  // wave-uniform
+                const float dx = mx - fx[k];
+                const float dy = my - fy[k];
+                const float e2 = splat_e2(qa, qb, qc, dx, dy);
+                const float ex = __builtin_amdgcn_exp2f(e2);
+                const float araw = o * ex;
+                const float alpha = __builtin_amdgcn_fmed3f(araw, 0.f, amax);
+                // same decisions as the forward: before the pixel's last
+                // contributor and above the alpha gate
+                const bool live = pos < L[k] && alpha >= amin;
+                if (live) {
+                    any = true;
+                    const float iom = __builtin_amdgcn_rcpf(1.f - alpha);
+                    const float Tb = Tc[k] * iom;  // transmittance in front of this splat
+                    const float w = alpha * Tb;
+                    g_r = __builtin_fmaf(w, V0[k], g_r);
+                    g_g = __builtin_fmaf(w, V1[k], g_g);
+                    g_b = __builtin_fmaf(w, V2[k], g_b);
+                    const float Vc = __builtin_fmaf(V2[k], cb, __builtin_fmaf(V1[k], cg, V0[k] * cr));
+                    // dL/dalpha = T (dL/dC . c) - (dL/dC . S) / (1 - alpha)
+                    const float va = __builtin_fmaf(Tb, Vc, -(iom * VS[k]));
+                    VS[k] = __builtin_fmaf(w, Vc, VS[k]);
+                    Tc[k] = Tb;
+                    const float q = araw < amax ? va * ex : 0.f;  // clamped alpha passes no gradient
+                    g_o += q;
+                    const float qx = q * dx, qy = q * dy;
+                    m_x += qx;
+                    m_y += qy;
+                    m_xx = __builtin_fmaf(qx, dx, m_xx);
+                    m_xy = __builtin_fmaf(qx, dy, m_xy);
+                    m_yy = __builtin_fmaf(qy, dy, m_yy);
                 }
             }
             if (__ballot(any) == 0) continue;
-            const float E = wave_sums_t(a);
-            const float QX = dpp_f<0x150>(E), QY = dpp_f<0x154>(E);  // lanes 0 and 4 of the row: m_x, m_y
+            // wave totals of the nine sums in one transposed butterfly
+            const float E = wave_sum9_t(m_x, m_y, m_xx, m_xy, m_yy, g_o, g_r, g_g, g_b);
+            const float QX = bcast(E, 0), QY = bcast(E, 4);  // lanes holding m_x, m_y
             if (comp >= 0) {
                 // With vs = -o q the sums of vs dx, vs dy, ... are -o times the
                 // moments; A = -2 a / log2(e), B = -b / log2(e), C = -2 c / log2(e).
-                const bool second = lane >= kWave / 2;
-                const float o = second ? f0[1].z : f0[0].z;
-                const float qa = second ? f1[1].x : f1[0].x, qb = second ? f1[1].y : f1[0].y,
-                            qc = second ? f1[1].z : f1[0].z;
                 const float mean = __builtin_fmaf(__builtin_fmaf(ua, qa, ub * qb), QX,
                                                   __builtin_fmaf(vb, qb, vc * qc) * QY);
                 const float val = __builtin_fmaf(o * kLn2, mean, E * __builtin_fmaf(kS, o, kE));
-                const uint32_t p0 = (uint32_t)bcast((int)id, i), p1 = (uint32_t)bcast((int)id, max(i - 1, 0));
-                const int64_t p = (second ? p1 : p0) & kPairMask;
-                if (val != 0.f) atomicAdd(grad + gstep * p, val);
+                const int64_t p = idb & kPairMask;
+                atomicAdd(comp < kGradGeo ? grad_geo + kGradGeo * p + comp
+                                          : grad_col + kGradCol * p + (comp - kGradGeo), val);
             }
+            g_r = g_g = g_b = g_o = 0.f;
+            m_x = m_y = m_xx = m_xy = m_yy = 0.f;
+            any = false;
         }
     }
 }
@@ -602,17 +569,11 @@ __device__ __forceinline__ void part_slot(int& slot, int& part) {
 }
 
 // The queue of a part's entries in LDS: (pair | mask << 28) and place in the
-// tile's list; at most 63 waiting plus one refill of PULL * 64.
-template <int PULL>
+// tile's list.
 struct PartRing {
-    static constexpr uint32_t kSize = 128 * PULL;
-    static_assert(kSize >= kWave - 1 + PULL * kWave, "ring");
-    uint32_t id[kSize];
-    uint32_t pos[kSize];
+    uint32_t id[kRing];
+    uint32_t pos[kRing];
 };
-// The backward's loads are of a list it reads every entry of: fewer in flight,
-// for a ring that leaves the LDS to four waves a SIMD.
-constexpr int kPullBwd = 4;
 
 template <int TW, int TH, bool LAZY>
 __global__ __launch_bounds__(64) void k_render_fwd_part(const float4* __restrict__ rec,
@@ -646,7 +607,7 @@ __global__ __launch_bounds__(64) void k_render_fwd_part(const float4* __restrict
     const uint32_t quads = TM::quads(part);
     const int s = ranges[2 * t], e = ranges[2 * t + 1];
     __shared__ BatchLds sb;
-    __shared__ PartRing<kPull> ring;
+    __shared__ PartRing ring;
     uint32_t lp[kPull], lm[kPull];
     // next: the first entry not yet taken; end: of the block's list (lazy) or
     // the tile's
@@ -695,8 +656,8 @@ __global__ __launch_bounds__(64) void k_render_fwd_part(const float4* __restrict
             const uint32_t below = __builtin_amdgcn_mbcnt_hi(
                 (uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
             if (hit) {
-                ring.id[(qt + below) % ring.kSize] = id;
-                ring.pos[(qt + below) % ring.kSize] = pos;
+                ring.id[(qt + below) % kRing] = id;
+                ring.pos[(qt + below) % kRing] = pos;
             }
             qt += (uint32_t)__popcll(bal);
         }
@@ -712,8 +673,8 @@ __global__ __launch_bounds__(64) void k_render_fwd_part(const float4* __restrict
         wave_lds_sync();
         id = pos = 0u;
         if (lane < got) {
-            id = ring.id[(qh + (uint32_t)lane) % ring.kSize];
-            pos = ring.pos[(qh + (uint32_t)lane) % ring.kSize];
+            id = ring.id[(qh + (uint32_t)lane) % kRing];
+            pos = ring.pos[(qh + (uint32_t)lane) % kRing];
         }
         qh += (uint32_t)got;
         return got;
@@ -773,327 +734,6 @@ __global__ __launch_bounds__(64) void k_render_fwd_part(const float4* __restrict
         out_T[pix] = T;
         out_last[pix] = last;
     }
-}
-
-// What the pixels of part `part` of heavy tile t carry down the list, their
-// transmittance Tc and VS, without the gradients: left at each segment's end
-// (`snap`), from where the segments are then walked at once.  A tile's sums are
-// those of a wave with the whole tile, bit for bit: a wave a part, each adding
-// its own sums, is as exact but rounds otherwise, and what cancels in the
-// sums of needle-like splats made that 1e-3 of the gradients' rms on single ones.
-template <int TW, int TH>
-__device__ __forceinline__ void chain_bwd(const BwdArgs& g, const ViewTable& vt, int t, int part, int slot,
-                                          BatchLds& sb, PartRing<kPullBwd>& ring) {
-    using TM = TileMap<TW, TH>;
-    const float4* __restrict__ rec = g.rec;
-    const int32_t* __restrict__ ids = g.ids;
-    const float* bg = g.bg;
-    const int v = tile_view(vt, t);
-    const int lt = t - vt.tile_off[v];
-    const int gx = vt.gx[v], W = vt.W[v], H = vt.H[v];
-    const int tx = lt % gx, ty = lt / gx;
-    const int lane = threadIdx.x;
-    const float b0 = bg ? bg[0] : 0.f, b1 = bg ? bg[1] : 0.f, b2 = bg ? bg[2] : 0.f;
-    int x, y;
-    TM::pixel(lane, part, x, y);
-    const int px = tx * TW + x, py = ty * TH + y;
-    const float fx = px + 0.5f, fy = py + 0.5f;
-    int L = 0;
-    float Tc = 1.f, V0 = 0.f, V1 = 0.f, V2 = 0.f;
-    if (px < W && py < H) {
-        const int64_t pix = (int64_t)vt.pix_off[v] + (int64_t)py * W + px;
-        L = g.last[pix];
-        Tc = g.T_final[pix];
-        V0 = g.v_rgb[3 * pix];
-        V1 = g.v_rgb[3 * pix + 1];
-        V2 = g.v_rgb[3 * pix + 2];
-    }
-    float VS = Tc * (V0 * b0 + V1 * b1 + V2 * b2);
-    const int s = g.ranges[2 * t], e = g.ranges[2 * t + 1];
-    int most = 0;  // the tile's largest `last`, which sets the segments
-#pragma unroll
-    for (int k = 0; k < TM::PPL; k++) {
-        int kx, ky;
-        TM::pixel(lane, k, kx, ky);
-        kx += tx * TW;
-        ky += ty * TH;
-        if (kx < W && ky < H) most = max(most, g.last[(int64_t)vt.pix_off[v] + (int64_t)ky * W + kx]);
-    }
-    // a pixel's last contributor lies inside its tile's list
-    most = min(__builtin_amdgcn_readfirstlane(wave_max_i(most)), e - s);
-    const int lmax = min(__builtin_amdgcn_readfirstlane(wave_max_i(L)), e - s);
-    if (lmax <= 0) return;
-    const int len = seg_length(g, most);
-    int seg = (lmax - 1) / len - 1;  // the next segment to end, at entry (seg + 1) len
-    if (seg < 0) return;
-    auto leave = [&]() {
-        float* p = snap_at<TW * TH>(g, slot, seg);
-        p[part * kWave + lane] = Tc;
-        p[TW * TH + part * kWave + lane] = VS;
-        seg--;
-    };
-    const float amin = g.rp.alpha_min, amax = g.rp.alpha_max;
-    const uint32_t quads = TM::quads(part);
-    uint32_t lp[kPullBwd];
-    int next = s + lmax - 1;  // the first entry not yet taken, walking down
-    uint32_t qh = 0, qt = 0;
-    auto pull = [&]() {
-#pragma unroll
-        for (int u = 0; u < kPullBwd; u++) lp[u] = (uint32_t)ids[max(next - u * kWave - lane, s)];
-    };
-    auto take = [&]() {
-#pragma unroll
-        for (int u = 0; u < kPullBwd; u++) {
-            const int j = next - u * kWave - lane;
-            const bool hit = j >= s && ((lp[u] >> kPairBits) & quads) != 0u;
-            const uint64_t bal = __ballot(hit);
-            const uint32_t below = __builtin_amdgcn_mbcnt_hi(
-                (uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-            if (hit) {
-                ring.id[(qt + below) % ring.kSize] = lp[u];
-                ring.pos[(qt + below) % ring.kSize] = (uint32_t)(j - s);
-            }
-            qt += (uint32_t)__popcll(bal);
-        }
-        next -= kPullBwd * kWave;
-    };
-    auto draw = [&](uint32_t& id, uint32_t& pos) -> int {
-        while (qt - qh < (uint32_t)kWave && next >= s) {
-            take();
-            if (next >= s) pull();
-        }
-        const int got = (int)min(qt - qh, (uint32_t)kWave);
-        wave_lds_sync();
-        id = pos = 0u;
-        if (lane < got) {
-            id = ring.id[(qh + (uint32_t)lane) % ring.kSize];
-            pos = ring.pos[(qh + (uint32_t)lane) % ring.kSize];
-        }
-        qh += (uint32_t)got;
-        return got;
-    };
-    pull();
-    uint32_t id, pos;
-    int nb = draw(id, pos);
-    LaneSplat ls = {};
-    if (lane < nb) ls = load_splat(rec, id & kPairMask);
-    while (nb > 0) {
-        wave_lds_sync();  // the previous batch is read
-        stage_splat(sb, ls);
-        sb.f[2][lane].z = __uint_as_float(pos);
-        ls = {};
-        const int nn = draw(id, pos);
-        if (lane < nn) ls = load_splat(rec, id & kPairMask);
-        wave_lds_sync();
-        for (int i = 0; i < nb; i += kGroup) {
-            float al[kGroup], iom[kGroup], Vc[kGroup];
-            int at[kGroup];
-            bool live[kGroup];
-#pragma unroll
-            for (int u = 0; u < kGroup; u++) {
-                const float4 f0 = sb.f[0][i + u], f1 = sb.f[1][i + u], f2 = sb.f[2][i + u];
-                const float dx = f0.x - fx;
-                const float dy = f0.y - fy;
-                const float ex = __builtin_amdgcn_exp2f(splat_e2(f1.x, f1.y, f1.z, dx, dy));
-                al[u] = __builtin_amdgcn_fmed3f(f0.z * ex, 0.f, amax);
-                iom[u] = __builtin_amdgcn_rcpf(1.f - al[u]);
-                Vc[u] = __builtin_fmaf(V2, f2.y, __builtin_fmaf(V1, f2.x, V0 * f1.w));
-                at[u] = (int)__float_as_uint(f2.z);
-                live[u] = at[u] < L && al[u] >= amin;
-            }
-            auto step = [&](int u) {
-                const float Tb = Tc * iom[u];  // transmittance in front of this splat
-                VS = live[u] ? __builtin_fmaf(al[u] * Tb, Vc[u], VS) : VS;
-                Tc = live[u] ? Tb : Tc;
-            };
-            // (of a short last group, the unused entries' alpha is zero)
-            const int rest = min(kGroup, nb - i);
-            const int lowest = (int)__builtin_amdgcn_readfirstlane(__float_as_uint(sb.f[2][i + rest - 1].z));
-            if (lowest >= (seg + 1) * len) {
-#pragma unroll
-                for (int u = 0; u < kGroup; u++) step(u);
-            } else {
-#pragma unroll
-                for (int u = 0; u < kGroup; u++) {
-                    const int p = __builtin_amdgcn_readfirstlane(at[u]);
-                    if (u < rest)
-                        while (seg >= 0 && p < (seg + 1) * len) leave();
-                    step(u);
-                }
-                if (seg < 0) return;
-            }
-        }
-        nb = nn;
-    }
-    while (seg >= 0) leave();
-}
-
-// ---- the backward's launch
-//
-// Tiles differ a hundredfold in the entries their pixels reach back through,
-// and a wave has a tile to itself: the launch lasted as long as its heaviest
-// tiles, with the CUs busy three quarters of it on the 150-camera step and a
-// fifth of it on 256 tiles.  So the tiles are launched heaviest first by what
-// the backward will walk (the largest `last` of a tile's pixels, read here
-// from the image the caller passes), and those much heavier than a wave's fair
-// share of the launch are walked in segments at once, from the states that a
-// chain over the list left at the segments' ends (chain_bwd).
-// Weights are bucketed, 16 buckets an octave like gs_settings.tile_order's.
-// us, a wave per tile in the settings' order -> this (weights and plan, 20-30
-// us, not counted): 4 x 1237x822 920 -> 690, 4 x 1600x1066 (32x16) 1250 -> 1065, 8
-// uneven views 1149 -> 1185, one 1237x822 view of blobs 346 -> 303.
-constexpr int kWeightBuckets = 513;
-constexpr int kWeightThreads = 1024;
-constexpr int kWaveSlots = 4096;  // waves of the backward the chip holds at once
-// A tile is heavy past kShare times the launch's weight over kWaveSlots; so at
-// most kWaveSlots / kShare tiles are.  The chain is work on top of the tile's
-// own, about half of it, so too many are a loss and too few leave the tail: us
-// at kShare 2, 3, 4 on 4 x 1237x822 803, 686, 692, on 4 x 1600x1066 1240, 1065,
-// 1041, on 8 uneven views 1103, 1189, 1185, on one 1237x822 view of blobs 240, 303,
-// 354.
-constexpr int kShare = 3;
-constexpr int kMaxHeavy = kBwdHeavy;
-static_assert(kMaxHeavy >= kWaveSlots / kShare, "as many as can pass kShare");
-
-// (walked entries, their bucket; no entries: bucket 0)
-__device__ __forceinline__ uint32_t weight_bucket(uint32_t n) {
-    if (n == 0) return 0;
-    const int lg = 31 - __clz((int)n);
-    const uint32_t m = lg >= 4 ? (n >> (lg - 4)) & 15u : (n << (4 - lg)) & 15u;
-    return 1u + 16u * (uint32_t)lg + m;
-}
-
-__device__ __forceinline__ float bucket_weight(int b) {  // of a bucket's lower end
-    return b <= 0 ? 0.f : __builtin_ldexpf(1.f + (float)((b - 1) & 15) / 16.f, (b - 1) >> 4);
-}
-
-// each tile's weight bucket, a wave per tile
-template <int TW, int TH>
-__global__ __launch_bounds__(256) void k_bwd_weights(ViewTable vt, const int32_t* __restrict__ ranges,
-                                                     const int32_t* __restrict__ last, int T,
-                                                     uint32_t* __restrict__ bucket) {
-    using TM = TileMap<TW, TH>;
-    const int t = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + threadIdx.x / kWave));
-    const int lane = threadIdx.x % kWave;
-    if (t >= T) return;
-    const int v = tile_view(vt, t);
-    const int lt = t - vt.tile_off[v];
-    const int gx = vt.gx[v], W = vt.W[v], H = vt.H[v];
-    const int tx = lt % gx, ty = lt / gx;
-    int m = 0;
-#pragma unroll
-    for (int k = 0; k < TM::PPL; k++) {
-        int x, y;
-        TM::pixel(lane, k, x, y);
-        const int px = tx * TW + x, py = ty * TH + y;
-        if (px < W && py < H) m = max(m, last[(int64_t)vt.pix_off[v] + (int64_t)py * W + px]);
-    }
-    m = min(wave_max_i(m), ranges[2 * t + 1] - ranges[2 * t]);
-    if (lane == 0) bucket[t] = weight_bucket((uint32_t)max(m, 0));
-}
-
-// The order of the tiles with anything to walk, heaviest bucket first, their
-// number and the heavy ones' (plan[0], plan[1]).  One workgroup; each thread
-// keeps kHold tiles' loads in flight (12 us on 16224 tiles).
-__global__ __launch_bounds__(kWeightThreads) void k_bwd_plan(const uint32_t* __restrict__ bucket, int T,
-                                                             uint32_t* __restrict__ order,
-                                                             uint32_t* __restrict__ plan) {
-    constexpr int kHold = 8;
-    __shared__ uint32_t s_n[kWeightBuckets];
-    __shared__ uint32_t s_w[kWeightThreads / kWave];
-    __shared__ float s_t[kWeightThreads / kWave];
-    __shared__ uint32_t s_heavy;
-    const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
-    if (tid < kWeightBuckets) s_n[tid] = 0;
-    if (tid == 0) s_heavy = 0;
-    __syncthreads();
-    auto each = [&](auto f) {
-        for (int t0 = 0; t0 < T; t0 += kHold * kWeightThreads) {
-            uint32_t b[kHold];
-#pragma unroll
-            for (int h = 0; h < kHold; h++) {
-                const int t = t0 + h * kWeightThreads + tid;
-                b[h] = t < T ? bucket[t] : 0u;
-            }
-#pragma unroll
-            for (int h = 0; h < kHold; h++)
-                if (b[h]) f(t0 + h * kWeightThreads + tid, b[h]);
-        }
-    };
-    each([&](int, uint32_t b) { atomicAdd(&s_n[b], 1u); });
-    __syncthreads();
-    // exclusive scan from the heaviest bucket down: thread i takes bucket
-    // kWeightBuckets - 1 - i; and the launch's whole weight
-    const int qb = kWeightBuckets - 1 - tid;
-    const uint32_t c = qb > 0 ? s_n[qb] : 0u;
-    const float mine = (float)c * bucket_weight(qb);
-    uint32_t inc = c;
-    float tot = mine;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const uint32_t x = __shfl_up(inc, off, kWave);
-        if (lane >= off) inc += x;
-        tot += __shfl_xor(tot, off, kWave);
-    }
-    if (lane == kWave - 1) {
-        s_w[w] = inc;
-        s_t[w] = tot;
-    }
-    __syncthreads();
-    uint32_t before = 0, all = 0;
-    tot = 0.f;
-    for (int i = 0; i < kWeightThreads / kWave; i++) {
-        if (i < w) before += s_w[i];
-        all += s_w[i];
-        tot += s_t[i];
-    }
-    if (qb > 0) {
-        s_n[qb] = before + inc - c;
-        if (c && bucket_weight(qb) * kWaveSlots > kShare * tot) atomicMax(&s_heavy, before + inc);
-    }
-    __syncthreads();
-    if (tid == 0) {
-        plan[0] = all;
-        plan[1] = min(s_heavy, (uint32_t)kMaxHeavy);
-    }
-    each([&](int t, uint32_t b) { order[atomicAdd(&s_n[b], 1u)] = (uint32_t)t; });
-}
-
-// The heavy tiles' chains first (a tile's parts kXcds workgroups apart, so they
-// share an L2), then the other tiles, whole.  Without a plan (plan NULL) the
-// first `heavy` tiles are.
-template <int TW, int TH>
-__global__ __launch_bounds__(64) void k_render_bwd(BwdArgs g, ViewTable vt, int T,
-                                                   const uint32_t* __restrict__ order,
-                                                   const uint32_t* __restrict__ plan, int heavy) {
-    constexpr int PPL = TileMap<TW, TH>::PPL;
-    __shared__ BatchLds sb;
-    __shared__ PartRing<kPullBwd> ring;
-    const int n = plan ? (int)plan[0] : T;
-    if (plan) heavy = (int)plan[1];
-    const int x = blockIdx.x;
-    const int parts = (heavy + kXcds - 1) / kXcds * kXcds * PPL;
-    if (x < parts) {
-        const int slot = x / (kXcds * PPL) * kXcds + x % kXcds;
-        if (slot >= heavy) return;
-        chain_bwd<TW, TH>(g, vt, order ? (int)order[slot] : slot, x / kXcds % PPL, slot, sb, ring);
-    } else {
-        const int slot = heavy + x - parts;
-        if (slot >= n) return;
-        tile_bwd<TW, TH, false>(g, vt, order ? (int)order[slot] : slot, sb);
-    }
-}
-
-// The heavy tiles' segments, a wave each.
-template <int TW, int TH>
-__global__ __launch_bounds__(64) void k_render_bwd_segs(BwdArgs g, ViewTable vt, const uint32_t* __restrict__ order,
-                                                        const uint32_t* __restrict__ plan, int heavy) {
-    __shared__ BatchLds sb;
-    if (plan) heavy = (int)plan[1];
-    const int x = blockIdx.x;
-    const int slot = x / (kXcds * g.segs) * kXcds + x % kXcds;
-    if (slot >= heavy) return;
-    tile_bwd<TW, TH, true>(g, vt, order ? (int)order[slot] : slot, sb, slot, x / kXcds % g.segs);
 }
 
 constexpr int kL1Blocks = 1024;
@@ -1171,37 +811,14 @@ hipError_t fwd_impl(Ctx* c, const ViewTable& vt, const RasterParams& rp, const f
     return e;
 }
 
-// Tiles whose chains are all resident at once are all walked in segments, unplanned
-// (256 tiles of 16x16, 10k blob splats 514 -> 178 us; 476 of 32x16, 1.4M splats 1290);
-// more are planned.  Past 2^20 tiles (the plan is one workgroup's) none is split.
 template <int TW, int TH>
 hipError_t bwd_impl(Ctx* c, const ViewTable& vt, const RasterParams& rp, const float* bg,
-                    const float* T_final, const int32_t* last, const float* v_rgb, hipStream_t st) {
-    constexpr int PPL = TileMap<TW, TH>::PPL;
-    const int T = (int)c->n_tiles;
-    const int all = (int64_t)T * PPL <= kWaveSlots ? T : 0;
-    const BwdArgs g = {reinterpret_cast<const float4*>(c->rec), reinterpret_cast<const int32_t*>(c->tids),
-                       c->tranges, bg, T_final, last, v_rgb, c->grad2d,
-                       c->grad2d + kGradGeo * c->cap.max_pairs, c->snap, all ? 2 * kBwdSegs : kBwdSegs, rp};
-    const auto segments = [&](int tiles, const uint32_t* order, const uint32_t* plan, int heavy) {
-        hipLaunchKernelGGL((k_render_bwd_segs<TW, TH>), dim3((unsigned)((tiles + kXcds - 1) / kXcds * kXcds * g.segs)),
-                           dim3(64), 0, st, g, vt, order, plan, heavy);
-    };
-    if (all || T > (1 << 20)) {
-        const unsigned grid = all ? (unsigned)((T + kXcds - 1) / kXcds * kXcds * PPL) : (unsigned)T;
-        hipLaunchKernelGGL((k_render_bwd<TW, TH>), dim3(grid), dim3(64), 0, st, g, vt, T, nullptr, nullptr, all);
-        if (all) segments(T, nullptr, nullptr, all);
-        return hipGetLastError();
-    }
-    uint32_t* bucket = c->tk[0];
-    uint32_t* order = c->tk[1];
-    uint32_t* plan = c->scalars + kScalarPlan;
-    hipLaunchKernelGGL((k_bwd_weights<TW, TH>), dim3((unsigned)((T + 3) / 4)), dim3(256), 0, st, vt, c->tranges,
-                       last, T, bucket);
-    hipLaunchKernelGGL(k_bwd_plan, dim3(1), dim3(kWeightThreads), 0, st, bucket, T, order, plan);
-    const unsigned grid = (unsigned)(T + (PPL - 1) * std::min(T, kMaxHeavy) + kXcds * PPL);
-    hipLaunchKernelGGL((k_render_bwd<TW, TH>), dim3(grid), dim3(64), 0, st, g, vt, T, order, plan, 0);
-    segments(std::min(T, kMaxHeavy), order, plan, 0);
+                    const float* T_final, const int32_t* last, const float* v_rgb,
+                    const uint32_t* order, int mode, hipStream_t st) {
+    hipLaunchKernelGGL((k_render_bwd<TW, TH>), dim3(raster_grid(c, vt, mode)), dim3(64), 0, st,
+                       reinterpret_cast<const float4*>(c->rec), reinterpret_cast<const int32_t*>(c->tids), c->tranges, order,
+                       vt, rp, bg, T_final, last, v_rgb, c->grad2d,
+                       c->grad2d + kGradGeo * c->cap.max_pairs, mode);
     return hipGetLastError();
 }
 
@@ -1229,11 +846,13 @@ hipError_t launch_render_bwd(Ctx* c, const ViewTable& vt, const RasterParams& rp
         const hipError_t e = launch_expand_lists(c, st);
         if (e != hipSuccess) return e;
     }
+    const uint32_t* order = c->ordered ? c->tile_order : nullptr;
+    const int mode = rp.tile_order == 2 ? 2 : (order ? 1 : 0);
     const int TW = rp.tile_w, TH = rp.tile_h;
-    if (TW == 16 && TH == 16) return bwd_impl<16, 16>(c, vt, rp, bg, T_final, last, v_rgb, st);
-    if (TW == 16 && TH == 8) return bwd_impl<16, 8>(c, vt, rp, bg, T_final, last, v_rgb, st);
-    if (TW == 8 && TH == 8) return bwd_impl<8, 8>(c, vt, rp, bg, T_final, last, v_rgb, st);
-    if (TW == 32 && TH == 16) return bwd_impl<32, 16>(c, vt, rp, bg, T_final, last, v_rgb, st);
+    if (TW == 16 && TH == 16) return bwd_impl<16, 16>(c, vt, rp, bg, T_final, last, v_rgb, order, mode, st);
+    if (TW == 16 && TH == 8) return bwd_impl<16, 8>(c, vt, rp, bg, T_final, last, v_rgb, order, mode, st);
+    if (TW == 8 && TH == 8) return bwd_impl<8, 8>(c, vt, rp, bg, T_final, last, v_rgb, order, mode, st);
+    if (TW == 32 && TH == 16) return bwd_impl<32, 16>(c, vt, rp, bg, T_final, last, v_rgb, order, mode, st);
     return hipErrorInvalidValue;
 }
 

@@ -1,0 +1,63 @@
+"""The raster backward runs the tiles in natural order where the settings say so
+(gs_settings.tile_order = 0).  A splat's tiles add their gradient sums in floats
+as they run, so the order shows in what an addition loses: the first tile of a
+4096x4096 view adds 2^28 of something to a splat over the whole view, the last
+takes it away, and thousands of tiles between (further from both than the chip
+holds waves at once) add 1 each.  In natural order every 1 is lost beside 2^28
+(less than a sixteenth of its last place) and nothing is left; run heaviest
+first, the tiles between, which a second splat makes the heavier, would come
+first and their sum stay."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+SIDE, TILE = 4096, 16
+BIG = 2.0 ** 28
+
+
+@pytest.fixture(scope="module")
+def gs():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2603_04847_amd as P
+    P.load()
+    return P
+
+
+def test_backward_runs_in_natural_order(gs):
+    from paper_2603_04847_amd.splat import Splatter
+    f = lambda a: torch.tensor(a, device="cuda", dtype=torch.float32)
+    fx = 300.0
+    # on the axis: one splat over the whole view, and behind it one 450 pixels
+    # wide (its alpha passes 1/255 out to 1400), which no corner meets
+    sd, z = np.array([20000.0, 450.0]), np.array([2.0, 3.0])
+    means = np.zeros((3, 2))
+    means[2] = z
+    quats = np.zeros((4, 2))
+    quats[0] = 1.0
+    params = dict(means=f(means), log_scales=f(np.tile(np.log(sd * z / fx), (3, 1))), quats=f(quats),
+                  opacity_logit=f([-3.9, 0.0]), sh=f(np.zeros((1, 3, 2))))
+    ctx = gs.Context(max_pairs=2, max_isect=400_000, max_tiles=(SIDE // TILE) ** 2, max_views=1)
+    sp = Splatter(ctx, gs.default_settings(tile_order=0))
+    view = np.eye(4)[None, :3].reshape(1, 12)
+    rgb, T, last, cams = sp.forward(params, 0, f(view), f([[fx, fx, SIDE / 2, SIDE / 2]]),
+                                    np.array([[SIDE, SIDE]], np.int32))
+    assert ctx.status()["flags"] == 0
+    last = last.view(SIDE, SIDE)
+    v = torch.zeros((SIDE, SIDE, 3), device="cuda")
+    p = TILE // 2
+    v[p, p, 0], v[SIDE - 1 - p, SIDE - 1 - p, 0] = BIG, -BIG  # mirror images: the same alpha
+    assert last[p, p] == last[SIDE - 1 - p, SIDE - 1 - p] == 1
+    y, x = slice(68 * TILE + p, 188 * TILE, TILE), slice(78 * TILE + p, 178 * TILE, TILE)
+    v[y, x, 0] = 1.0
+    assert last[y, x].min() == 2
+    n = v[y, x, 0].numel()
+    grads, _ = sp.backward(params, 0, cams, T, last.reshape(-1), v.reshape(-1, 3))
+    got = float(grads["sh"][0, 0, 0]) / 0.28209479177387814  # of the colour
+    ctx.close()
+    alpha = 1.0 / (1.0 + np.exp(3.9))
+    kept = got / (n * alpha)  # (alpha falls by 1% to the corners)
+    assert abs(kept) <= 0.05, kept
