@@ -146,6 +146,8 @@ __device__ __forceinline__ void view_dir(const GaussLocal& G, const Cam& cam, fl
 struct Proj {
     bool valid;
     double p[3], iz;      // camera-frame mean and 1 / z
+    double qn[4], qnorm;  // unit quaternion and the raw norm
+    float Rq[9];          // its rotation (rounded from double)
     double Sc[6];         // camera covariance (sym)
     float J00, J02, J11, J12;
     bool clx, cly;
@@ -155,30 +157,7 @@ struct Proj {
     float dir[3], dist;
 };
 
-// A Gaussian's unit quaternion (w, x, y, z) and its rotation, the same for every view.
-struct Rotation {
-    double qn[4], qnorm, R[9];
-};
-
-__device__ __forceinline__ void gauss_rotation(const GaussLocal& G, Rotation& Q) {
-    Q.qnorm = sqrt((double)G.q[0] * G.q[0] + (double)G.q[1] * G.q[1] + (double)G.q[2] * G.q[2] +
-                   (double)G.q[3] * G.q[3]);
-    const double inv = 1.0 / Q.qnorm;
-#pragma unroll
-    for (int k = 0; k < 4; k++) Q.qn[k] = G.q[k] * inv;
-    const double w = Q.qn[0], x = Q.qn[1], y = Q.qn[2], z = Q.qn[3];
-    Q.R[0] = 1.0 - 2.0 * (y * y + z * z);
-    Q.R[1] = 2.0 * (x * y - w * z);
-    Q.R[2] = 2.0 * (x * z + w * y);
-    Q.R[3] = 2.0 * (x * y + w * z);
-    Q.R[4] = 1.0 - 2.0 * (x * x + z * z);
-    Q.R[5] = 2.0 * (y * z - w * x);
-    Q.R[6] = 2.0 * (x * z - w * y);
-    Q.R[7] = 2.0 * (y * z + w * x);
-    Q.R[8] = 1.0 - 2.0 * (x * x + y * y);
-}
-
-__device__ __forceinline__ void project_one(const GaussLocal& G, const Rotation& Q, const Cam& cam, int W, int H,
+__device__ __forceinline__ void project_one(const GaussLocal& G, const Cam& cam, int W, int H,
                                             const RasterParams& rp, Proj& P) {
     P.valid = false;
 #pragma unroll
@@ -189,7 +168,27 @@ __device__ __forceinline__ void project_one(const GaussLocal& G, const Rotation&
     view_dir(G, cam, P.dir, P.dist);
     const double z = P.p[2];
     if (!(z >= rp.near_plane)) return;
-    const double (&Rq)[9] = Q.R;
+    // rotation of the unit quaternion (w, x, y, z)
+    P.qnorm = sqrt((double)G.q[0] * G.q[0] + (double)G.q[1] * G.q[1] + (double)G.q[2] * G.q[2] +
+                   (double)G.q[3] * G.q[3]);
+    const double inv = 1.0 / P.qnorm;
+#pragma unroll
+    for (int k = 0; k < 4; k++) P.qn[k] = G.q[k] * inv;
+    double Rq[9];
+    {
+        const double w = P.qn[0], x = P.qn[1], y = P.qn[2], zq = P.qn[3];
+        Rq[0] = 1.0 - 2.0 * (y * y + zq * zq);
+        Rq[1] = 2.0 * (x * y - w * zq);
+        Rq[2] = 2.0 * (x * zq + w * y);
+        Rq[3] = 2.0 * (x * y + w * zq);
+        Rq[4] = 1.0 - 2.0 * (x * x + zq * zq);
+        Rq[5] = 2.0 * (y * zq - w * x);
+        Rq[6] = 2.0 * (x * zq - w * y);
+        Rq[7] = 2.0 * (y * zq + w * x);
+        Rq[8] = 1.0 - 2.0 * (x * x + y * y);
+    }
+#pragma unroll
+    for (int k = 0; k < 9; k++) P.Rq[k] = (float)Rq[k];
     // Sc = (R Rq S)(R Rq S)^T
     double RM[9];  // R Rq S
 #pragma unroll
@@ -284,12 +283,10 @@ __global__ __launch_bounds__(kBlock) void k_project_fwd(gs_gaussians g, const fl
 #pragma unroll
         for (int ch = 0; ch < 3; ch++) bad |= !isfinite(sh[k][ch]);
     bool nonfinite = bad;
-    Rotation Q;
-    gauss_rotation(G, Q);
     for (int v = 0; v < vt.V; v++) {
         const Cam cam = load_cam(viewmat, intr, vt.cam[v]);
         Proj P;
-        if (!bad) project_one(G, Q, cam, vt.W[v], vt.H[v], rp, P);
+        if (!bad) project_one(G, cam, vt.W[v], vt.H[v], rp, P);
         bool keep = !bad && P.valid && G.o > rp.alpha_min;
         float4 r0 = make_float4(0.f, 0.f, 0.f, 0.f);
         if (keep) {
@@ -516,11 +513,6 @@ __global__ __launch_bounds__(kBlock) void k_project_bwd_color(gs_gaussians g, co
         if (s_acc[k] != 0.0) atomicAdd(&twist_acc[k], s_acc[k]);
 }
 
-// The geometry pass: bound by its arithmetic in double at two waves a SIMD (201
-// registers; three waves spill: 503 us for the 400 below).  So the rotation is
-// made once a Gaussian, and what is linear in the covariance's gradient (scales,
-// quaternion) once for all views from the sum in world axes: 3M Gaussians in 8
-// views 475 -> 400 us, 5M in 4 with Adam 495 -> 460, 1M in 4 150 -> 135.
 template <bool ADAM>
 __global__ __launch_bounds__(kBlock) void k_project_bwd_geom(gs_gaussians g, const float* __restrict__ viewmat,
                                  const float* __restrict__ intr, ViewTable vt, RasterParams rp,
@@ -559,10 +551,6 @@ __global__ __launch_bounds__(kBlock) void k_project_bwd_geom(gs_gaussians g, con
             }
             float v_ls[3] = {0.f, 0.f, 0.f}, v_q[4] = {0.f, 0.f, 0.f, 0.f};
             float v_logit = 0.f;
-            Rotation Q;
-            if (active) gauss_rotation(G, Q);
-            double vSig[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // of the world covariance, all views
-            bool any = false;
             // the next view's 2D gradients are requested before this view's
             // chain runs, so their latency hides behind it
             RowOf<6> G9n = {};
@@ -583,7 +571,7 @@ __global__ __launch_bounds__(kBlock) void k_project_bwd_geom(gs_gaussians g, con
                         for (int k = 0; k < 6; k++) gp[k] = 0.f;  // leave the accumulator clean
                         const Cam cam = load_cam(viewmat, intr, vt.cam[v]);
                         Proj P;
-                        project_one(G, Q, cam, vt.W[v], vt.H[v], rp, P);
+                        project_one(G, cam, vt.W[v], vt.H[v], rp, P);
                         if (P.valid) {
                             // opacity
                             v_logit += G9[5] * G.o * (1.f - G.o);
@@ -654,69 +642,62 @@ __global__ __launch_bounds__(kBlock) void k_project_bwd_geom(gs_gaussians g, con
 #pragma unroll
                             for (int e = 0; e < 3; e++)
                                 v_mu[e] += (float)(cam.R[e] * vp[0] + cam.R[3 + e] * vp[1] + cam.R[6 + e] * vp[2]);
-                            // Sc = R Sig R^T: vSig = R^T vSc R, symmetric
-                            any = true;
-                            double SR[9];  // vSc R
+                            // Sc = R Sig R^T, Sig = M M^T, M = Rq S.  Q = Rq^T vSig Rq
+                            // = (R Rq)^T vSc (R Rq) (symmetric): the scale gradient is
+                            // 2 s_c^2 Q_cc and vR = 2 vSig Rq S^2 = 2 Rq Q S^2
+                            double Q[6];
+                            {
+                                double RR[9];  // R Rq
+#pragma unroll
+                                for (int r = 0; r < 3; r++)
+#pragma unroll
+                                    for (int c = 0; c < 3; c++)
+                                        RR[3 * r + c] = cam.R[3 * r] * P.Rq[c] + cam.R[3 * r + 1] * P.Rq[3 + c] +
+                                                        cam.R[3 * r + 2] * P.Rq[6 + c];
+                                int k = 0;
+#pragma unroll
+                                for (int r = 0; r < 3; r++)
+#pragma unroll
+                                    for (int c = r; c < 3; c++) {
+                                        double acc = 0.0;
+#pragma unroll
+                                        for (int m = 0; m < 3; m++)
+#pragma unroll
+                                            for (int n = 0; n < 3; n++)
+                                                acc += RR[3 * m + r] * symd(vSc, m, n) * RR[3 * n + c];
+                                        Q[k++] = acc;
+                                    }
+                            }
+                            const double s2[3] = {(double)G.s[0] * G.s[0], (double)G.s[1] * G.s[1],
+                                                  (double)G.s[2] * G.s[2]};
+#pragma unroll
+                            for (int c = 0; c < 3; c++) v_ls[c] += (float)(2.0 * symd(Q, c, c) * s2[c]);
+                            double vR[9];  // 2 Rq Q S^2
 #pragma unroll
                             for (int r = 0; r < 3; r++)
 #pragma unroll
                                 for (int c = 0; c < 3; c++)
-                                    SR[3 * r + c] = symd(vSc, r, 0) * cam.R[c] + symd(vSc, r, 1) * cam.R[3 + c] +
-                                                    symd(vSc, r, 2) * cam.R[6 + c];
-                            int k = 0;
+                                    vR[3 * r + c] = 2.0 * (P.Rq[3 * r] * symd(Q, 0, c) + P.Rq[3 * r + 1] * symd(Q, 1, c) +
+                                                           P.Rq[3 * r + 2] * symd(Q, 2, c)) * s2[c];
+                            const double w = P.qn[0], qx = P.qn[1], qy = P.qn[2], qz = P.qn[3];
+                            double vqn[4];
+                            vqn[0] = 2.0 * (-qz * vR[1] + qy * vR[2] + qz * vR[3] - qx * vR[5] - qy * vR[6] +
+                                            qx * vR[7]);
+                            vqn[1] = 2.0 * (qy * vR[1] + qz * vR[2] + qy * vR[3] - w * vR[5] + qz * vR[6] +
+                                            w * vR[7]) - 4.0 * qx * (vR[4] + vR[8]);
+                            vqn[2] = 2.0 * (qx * vR[1] + w * vR[2] + qx * vR[3] + qz * vR[5] - w * vR[6] +
+                                            qz * vR[7]) - 4.0 * qy * (vR[0] + vR[8]);
+                            vqn[3] = 2.0 * (-w * vR[1] + qx * vR[2] + w * vR[3] + qy * vR[5] + qx * vR[6] +
+                                            qy * vR[7]) - 4.0 * qz * (vR[0] + vR[4]);
+                            const double qd = P.qn[0] * vqn[0] + P.qn[1] * vqn[1] + P.qn[2] * vqn[2] +
+                                              P.qn[3] * vqn[3];
+                            const double iq = 1.0 / P.qnorm;
 #pragma unroll
-                            for (int r = 0; r < 3; r++)
-#pragma unroll
-                                for (int c = r; c < 3; c++)
-                                    vSig[k++] += cam.R[r] * SR[c] + cam.R[3 + r] * SR[3 + c] + cam.R[6 + r] * SR[6 + c];
+                            for (int e = 0; e < 4; e++) v_q[e] += (float)((vqn[e] - P.qn[e] * qd) * iq);
                         }
                     }
                 }
                 twist_reduce(v, tw);
-            }
-            if (active && any) {
-                // Sig = M M^T, M = Rq S.  With D = Rq^T vSig Rq (symmetric) the scale
-                // gradient is 2 s_c^2 D_cc and vR = 2 vSig Rq S^2 = 2 Rq D S^2; all
-                // linear in vSig, so once for all views (Rq rounded to float here)
-                float Rq[9];
-#pragma unroll
-                for (int e = 0; e < 9; e++) Rq[e] = (float)Q.R[e];
-                double SQ[9], D[6];
-#pragma unroll
-                for (int r = 0; r < 3; r++)
-#pragma unroll
-                    for (int c = 0; c < 3; c++)
-                        SQ[3 * r + c] = symd(vSig, r, 0) * Rq[c] + symd(vSig, r, 1) * Rq[3 + c] +
-                                        symd(vSig, r, 2) * Rq[6 + c];
-                int k = 0;
-#pragma unroll
-                for (int r = 0; r < 3; r++)
-#pragma unroll
-                    for (int c = r; c < 3; c++)
-                        D[k++] = Rq[r] * SQ[c] + Rq[3 + r] * SQ[3 + c] + Rq[6 + r] * SQ[6 + c];
-                const double s2[3] = {(double)G.s[0] * G.s[0], (double)G.s[1] * G.s[1], (double)G.s[2] * G.s[2]};
-#pragma unroll
-                for (int c = 0; c < 3; c++) v_ls[c] = (float)(2.0 * symd(D, c, c) * s2[c]);
-                double vR[9];
-#pragma unroll
-                for (int r = 0; r < 3; r++)
-#pragma unroll
-                    for (int c = 0; c < 3; c++)
-                        vR[3 * r + c] = 2.0 * (Rq[3 * r] * symd(D, 0, c) + Rq[3 * r + 1] * symd(D, 1, c) +
-                                               Rq[3 * r + 2] * symd(D, 2, c)) * s2[c];
-                const double w = Q.qn[0], qx = Q.qn[1], qy = Q.qn[2], qz = Q.qn[3];
-                double vqn[4];
-                vqn[0] = 2.0 * (-qz * vR[1] + qy * vR[2] + qz * vR[3] - qx * vR[5] - qy * vR[6] + qx * vR[7]);
-                vqn[1] = 2.0 * (qy * vR[1] + qz * vR[2] + qy * vR[3] - w * vR[5] + qz * vR[6] + w * vR[7]) -
-                         4.0 * qx * (vR[4] + vR[8]);
-                vqn[2] = 2.0 * (qx * vR[1] + w * vR[2] + qx * vR[3] + qz * vR[5] - w * vR[6] + qz * vR[7]) -
-                         4.0 * qy * (vR[0] + vR[8]);
-                vqn[3] = 2.0 * (-w * vR[1] + qx * vR[2] + w * vR[3] + qy * vR[5] + qx * vR[6] + qy * vR[7]) -
-                         4.0 * qz * (vR[0] + vR[4]);
-                const double qd = Q.qn[0] * vqn[0] + Q.qn[1] * vqn[1] + Q.qn[2] * vqn[2] + Q.qn[3] * vqn[3];
-                const double iq = 1.0 / Q.qnorm;
-#pragma unroll
-                for (int e = 0; e < 4; e++) v_q[e] = (float)((vqn[e] - Q.qn[e] * qd) * iq);
             }
             if (active) {
                 const float gr[11] = {v_mu[0], v_mu[1], v_mu[2], v_ls[0], v_ls[1], v_ls[2],
