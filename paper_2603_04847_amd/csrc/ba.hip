@@ -59,8 +59,9 @@ constexpr int kRow = 12;
 enum { vX = 0, vR = 1, vR1 = 2, vP = 3, vP1 = 4, vAp = 5, vAp1 = 6, vAp2 = 7, vZ = 8, vCams = 9 };
 __host__ __device__ inline int64_t off_l(int n_cams) { return (int64_t)21 * n_cams; }
 __host__ __device__ inline int64_t off_vec(int n_cams, int v) { return (int64_t)(42 + 6 * v) * n_cams; }
-// scalars (sRZ: two, by the parity of the iteration; sPap: three, like A p)
-enum { sRZ = 0, sBB = 2, sDone = 3, sIt = 4, sCost = 5, sMasked = 6, sUnsorted = 7, sRR = 8, sPap = 9 };
+// scalars (sRZ and sEnd: two, by the parity of the iteration; sPap: three, like
+// A p).  sDone ends the two-pass path, sEnd k_ba_cg.
+enum { sRZ = 0, sBB = 2, sDone = 3, sIt = 4, sCost = 5, sMasked = 6, sUnsorted = 7, sRR = 8, sPap = 9, sEnd = 12 };
 // LDS of k_ba_cg: per camera its 16 floats, its 6 of p and its 6 sums of W u
 constexpr int kLdsPerCam = 16 * 4 + 6 * 8 + 6 * 8;
 constexpr int kLdsFixed = 2 * (kVec / kWave) * 8;
@@ -878,7 +879,7 @@ __device__ __forceinline__ void cg_open(int it, int n, double* __restrict__ cam,
         if (it == 0) sc[sBB] = bb;
         sc[sRR] = rr;
         sc[sIt] = (double)it;
-        if (done) sc[sDone] = 1.0;
+        sc[sEnd + (it & 1)] = done ? 1.0 : 0.0;
     }
 }
 
@@ -1007,14 +1008,20 @@ __global__ __launch_bounds__(kVec) void k_ba_cg(BaObs a, const int32_t* __restri
     double* s_acc = s_vec + 6 * n;                        // [6][n]: sum of W u
     float4* s_cam = reinterpret_cast<float4*>(s_acc + (LAST ? 0 : 6 * n));  // [n][4]
     const int tid = threadIdx.x;
-    if (!LAST && sc[sDone] > 0.0) return;
+    // whether an earlier launch found the end: a word that no workgroup of this
+    // launch writes, so all waves of all workgroups see the same
+    const bool ended = it > 0 && sc[sEnd + ((it - 1) & 1)] > 0.0;
+    if (!LAST && ended) {
+        if (blockIdx.x == 0 && tid == 0) sc[sEnd + (it & 1)] = 1.0;
+        return;
+    }
     if (tid < n) {
         const CamData cd = load_cam(a, tid);
 #pragma unroll
         for (int q = 0; q < 4; q++) s_cam[cam_slot(tid, q)] = cd.q[q];
     }
     Cg g;
-    if (LAST && sc[sDone] > 0.0) {
+    if (LAST && ended) {
         g.done = true;
         g.rr = sc[sRR];
         g.bb = sc[sBB];
