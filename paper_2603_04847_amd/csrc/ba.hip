@@ -108,19 +108,14 @@ __device__ __forceinline__ CamData lds_cam(const float4* s_cam, int c) {
     return d;
 }
 
-// 1/x and 1/sqrt(x) of normal positive x: the hardware's estimate (about 2^-26)
-// and two Newton steps, which leave an ulp or two where the library's correctly
-// rounded forms take twice the instructions.
+// 1/x of normal positive x: the hardware's estimate (about 2^-26) and two Newton
+// steps, the second of which rounds correctly what the first left within an ulp
+// or two, in half the instructions of a division, which also minds the ends of
+// the range.
 __device__ __forceinline__ double recip(double x) {
     double y = __builtin_amdgcn_rcp(x);
     y = fma(fma(-x, y, 1.0), y, y);
     return fma(fma(-x, y, 1.0), y, y);
-}
-
-__device__ __forceinline__ double recip_sqrt(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
-    return fma(0.5 * y, fma(-x * y, y, 1.0), y);
 }
 
 // Projection of one observation: camera point p, J_pi = [[a00, 0, a02],
@@ -151,9 +146,9 @@ __device__ __forceinline__ void project(const BaObs& a, const CamData& cam, doub
         P.w = 1.0;
         P.rho = s;
     } else {
-        const double ri = recip_sqrt(s);
-        P.w = a.delta * ri;
-        P.rho = 2.0 * a.delta * (s * ri) - a.delta * a.delta;
+        const double rs = sqrt(s);
+        P.w = a.delta / rs;
+        P.rho = 2.0 * a.delta * rs - a.delta * a.delta;
     }
     P.a00 = fx * iz;
     P.a02 = -P.a00 * u;
