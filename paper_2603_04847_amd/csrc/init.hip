@@ -298,6 +298,7 @@ struct Search {
             const float ez = fmaxf(fmaxf(lo.z - ghi[r][2], glo[r][2] - hi.z), 0.f);
             near |= __builtin_fmaf(ex, ex, __builtin_fmaf(ey, ey, ez * ez)) <= bcast(rb, 16 * r);
         }
+        near = near && lane < width;  // (no box is near only where the bounds are finite)
         if (D == 1) {
             const int l = c0 + lane - NL;
             near = near && l < nl && (unsigned)(l - l0) >= (unsigned)(l1 - l0);
