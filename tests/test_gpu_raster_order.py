@@ -6,7 +6,9 @@ takes it away, and thousands of tiles between (further from both than the chip
 holds waves at once) add 1 each.  In natural order every 1 is lost beside 2^28
 (less than a sixteenth of its last place) and nothing is left; run heaviest
 first, the tiles between, which a second splat makes the heavier, would come
-first and their sum stay."""
+first and their sum stay.  A wave that waits long for its first loads may add
+out of turn, so one of eight passes has to show the order; heaviest first, none
+would."""
 
 import numpy as np
 import pytest
@@ -55,9 +57,11 @@ def test_backward_runs_in_natural_order(gs):
     v[y, x, 0] = 1.0
     assert last[y, x].min() == 2
     n = v[y, x, 0].numel()
-    grads, _ = sp.backward(params, 0, cams, T, last.reshape(-1), v.reshape(-1, 3))
-    got = float(grads["sh"][0, 0, 0]) / 0.28209479177387814  # of the colour
-    ctx.close()
     alpha = 1.0 / (1.0 + np.exp(3.9))
-    kept = got / (n * alpha)  # (alpha falls by 1% to the corners)
-    assert abs(kept) <= 0.05, kept
+    kept = []
+    for _ in range(8):
+        grads, _ = sp.backward(params, 0, cams, T, last.reshape(-1), v.reshape(-1, 3))
+        got = float(grads["sh"][0, 0, 0]) / 0.28209479177387814  # of the colour
+        kept.append(got / (n * alpha))  # (alpha falls by 1% to the corners)
+    ctx.close()
+    assert min(abs(x) for x in kept) <= 0.05, kept
