@@ -1,14 +1,14 @@
 """The raster backward runs the tiles in natural order where the settings say so
 (gs_settings.tile_order = 0).  A splat's tiles add their gradient sums in floats
-as they run, so the order shows in what an addition loses: the first tile of a
-4096x4096 view adds 2^28 of something to a splat over the whole view, the last
-takes it away, and thousands of tiles between (further from both than the chip
-holds waves at once) add 1 each.  In natural order every 1 is lost beside 2^28
-(less than a sixteenth of its last place) and nothing is left; run heaviest
-first, the tiles between, which a second splat makes the heavier, would come
-first and their sum stay.  A wave that waits long for its first loads may add
-out of turn, so one of eight passes has to show the order; heaviest first, none
-would."""
+as they run, so the order shows in what an addition loses: the first eight tiles
+of a 4096x4096 view (one on each die, whose starts are not at one time) add 2^25
+each of something to a splat over the whole view, the last eight take it away,
+and thousands of tiles between (further from both than the chip holds waves at
+once) add 1 each.  In natural order every 1 is lost beside the large sum (less
+than an eighth of its last place) and nothing is left but that place; run
+heaviest first, the tiles between, which a second splat makes the heavier, would
+come first and their sum stay.  Waves may add out of turn, so one of eight
+passes has to show the order; heaviest first, none would."""
 
 import numpy as np
 import pytest
@@ -17,7 +17,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 SIDE, TILE = 4096, 16
-BIG = 2.0 ** 28
+BIG = 2.0 ** 25
 
 
 @pytest.fixture(scope="module")
@@ -51,8 +51,10 @@ def test_backward_runs_in_natural_order(gs):
     last = last.view(SIDE, SIDE)
     v = torch.zeros((SIDE, SIDE, 3), device="cuda")
     p = TILE // 2
-    v[p, p, 0], v[SIDE - 1 - p, SIDE - 1 - p, 0] = BIG, -BIG  # mirror images: the same alpha
-    assert last[p, p] == last[SIDE - 1 - p, SIDE - 1 - p] == 1
+    q = slice(p, 8 * TILE, TILE)
+    v[p, q, 0] = BIG
+    v[SIDE - 1 - p, SIDE - 8 * TILE + TILE - 1 - p::TILE, 0] = -BIG  # mirror images: the same alpha
+    assert torch.count_nonzero(v) == 16 and last[p, q].max() == 1
     y, x = slice(68 * TILE + p, 188 * TILE, TILE), slice(78 * TILE + p, 178 * TILE, TILE)
     v[y, x, 0] = 1.0
     assert last[y, x].min() == 2
