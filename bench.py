@@ -691,7 +691,8 @@ def _bench_line(raw, name):
 # the kernels of each timed call (bin_sort: every dispatch from k_count to k_chunk_expand)
 CALL_KERNELS = {
     "project": lambda k: k.startswith("k_project_fwd<"),
-    "render_fwd": lambda k: k.startswith("k_render_fwd_part<"),
+    "render_fwd": lambda k: k.startswith("k_render_fwd_part<") or (
+        k.startswith("k_render_fwd<") and k.split(", ")[2] == "false"),  # (true: the counting one)
     "raster_bwd": lambda k: k.startswith("k_render_bwd"),
     "photo": lambda k: k == "k_photo",
     "project_bwd_adam": lambda k: k in ("k_project_bwd_color<3, true>", "k_project_bwd_geom<true>"),
@@ -869,8 +870,8 @@ def summarize_trace(raw, workload, cmd, stem=None):
     if line:
         roof = line.get("roofline") or {}
         dom = roof.get("kernel")
-        kname = {"raster_bwd": "k_render_bwd", "render_fwd": "k_render_fwd"}.get(dom)
-        tr = [v for k, v in trace_avg.items() if kname and k.startswith(kname) and "_stats" not in k]
+        sel = CALL_KERNELS.get(dom) if dom in ("raster_bwd", "render_fwd") else None
+        tr = [v for k, v in trace_avg.items() if sel and sel(k)]
         md += ["", f"Workload: {line['config']['workload']}; tile {line['config']['tile']}, order "
                f"{line['config']['tile_order']}.", "",
                f"Agreement with the live timing: the same run's bench line measured `{dom}` at "

@@ -144,11 +144,11 @@ constexpr int kPull = 8;
 constexpr uint32_t kRing = 1024;
 static_assert(kRing >= kWave - 1 + kPull * kWave, "ring");
 
-// The counting forward (gs_settings.eval_stats): a wave per tile, PPL pixels a
-// lane, which also counts what the tile read and evaluated.  The plain forward
-// is k_render_fwd_part below; both give the same image bit for bit.
-template <int TW, int TH, bool LAZY>
-__global__ __launch_bounds__(64) void k_render_fwd_stats(const float4* __restrict__ rec,
+// The forward by a wave per tile, PPL pixels a lane; with EVALS
+// (gs_settings.eval_stats) it also counts what the tile read and evaluated.
+// k_render_fwd_part below gives the same image bit for bit.
+template <int TW, int TH, bool EVALS, bool LAZY>
+__global__ __launch_bounds__(64) void k_render_fwd(const float4* __restrict__ rec,
                                                    const int32_t* __restrict__ ids,
                                                    const int32_t* __restrict__ ranges,
                                                    const uint32_t* __restrict__ order, ViewTable vt,
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(64) void k_render_fwd_stats(const float4* __restric
 #pragma unroll
             for (int k = 0; k < PPL; k++) {
                 if (!(m & TM::quads(k))) continue;  // wave-uniform
-                qn[k]++;
+                if (EVALS) qn[k]++;
                 if (__ballot(gmin[k] <= 1.f) == 0) continue;  // wave-uniform: the slot has stopped
                 const float dx = mx - fx[k];
                 const float dy = my - fy[k];
@@ -332,8 +332,10 @@ __global__ __launch_bounds__(64) void k_render_fwd_stats(const float4* __restric
                     C2[k] = __builtin_fmaf(cb, w, C2[k]);
                     T[k] = Tn;
                     last[k] = pos;
-                    lastq[k] = qn[k];
-                    ncontrib++;
+                    if (EVALS) {
+                        lastq[k] = qn[k];
+                        ncontrib++;
+                    }
                 }
             }
         }
@@ -341,17 +343,19 @@ __global__ __launch_bounds__(64) void k_render_fwd_stats(const float4* __restric
     // workload statistics of the tile: contributing
     // (pixel, splat) pairs, list entries read, and (pixel, entry) evaluations
     // up to each pixel's last contributor over the entries covering its quadrant
-    int nev = 0;
+    if (EVALS) {
+        int nev = 0;
 #pragma unroll
-    for (int k = 0; k < PPL; k++) nev += lastq[k];
-    for (int sh = 32; sh > 0; sh >>= 1) {
-        ncontrib += __shfl_xor(ncontrib, sh, kWave);
-        nev += __shfl_xor(nev, sh, kWave);
-    }
-    if (lane == 0) {
-        tile_contrib[t] = ncontrib;
-        tile_entries[t] = nent;
-        tile_evals[t] = nev;
+        for (int k = 0; k < PPL; k++) nev += lastq[k];
+        for (int sh = 32; sh > 0; sh >>= 1) {
+            ncontrib += __shfl_xor(ncontrib, sh, kWave);
+            nev += __shfl_xor(nev, sh, kWave);
+        }
+        if (lane == 0) {
+            tile_contrib[t] = ncontrib;
+            tile_entries[t] = nent;
+            tile_evals[t] = nev;
+        }
     }
     const float b0 = bg ? bg[0] : 0.f, b1 = bg ? bg[1] : 0.f, b2 = bg ? bg[2] : 0.f;
 #pragma unroll
@@ -555,9 +559,26 @@ __global__ __launch_bounds__(64) void k_render_bwd(const float4* __restrict__ re
 // Forward, a wave per tile -> per part: 256x256 and 10k splats 84 -> 23 us (10k
 // blob splats 339 -> 97); 4 x 1237x822 (16x16 tiles) 519 -> 476; 8 uneven
 // views 977 -> 850; 4 x 1600x1066 (32x16) 1175 -> 930; one 1237x822 view 96 ->
-// 97: so every launch takes the parts.
+// 97.
 constexpr int kGroup = 4;
 static_assert(kWave % kGroup == 0, "groups fill a batch");
+
+// Which of the two forwards a launch takes.  Each part reads its tile's whole
+// list and gathers the records again, which pays where waves are few or a few
+// tiles hold the launch up.  Two tiles for each of the 4096 waves the chip takes
+// at once (four a SIMD) still leave it that; with several more the tiles' loads
+// even out over the waves, unless they are uneven as only many splats make
+// them, and a short list is mostly the part's own cost.  us, per tile and per
+// part, tiles and pairs a tile: one 2500x1700 view in 16x16 and 30k splats (16799,
+// 1.8) 200 and 258, 1M splats (60) whole calls of 627 and 665; 4 x 2000x1500 in
+// 16x16 (47k, 2.5) calls of 537 and 620; 8 x 1600x1066 in 16x16 and 300k blob
+// splats (53600, 45) 850 and 1096, in 32x16 (26800, 90) 1201 and 1223, smaller
+// splats 3421 and 1229; 4 x 1600x1066 in 32x16 and 30k blob splats (13400, 9)
+// 560 and 347; 8 uneven views (29186, 820) 977 and 850; one 4096x4096 view
+// (65536, 5) 858 and 1192.
+inline bool by_parts(int64_t tiles, int64_t pairs) {
+    return tiles <= 8192 || (tiles <= 32768 && pairs >= 8 * tiles);
+}
 
 // The slot and the part of this workgroup: a slot's parts are kXcds apart, so
 // they run together on one XCD.
@@ -785,7 +806,11 @@ void fwd_launch(Ctx* c, const ViewTable& vt, const RasterParams& rp, const float
     const unsigned slots = raster_grid(c, vt, mode);
     constexpr int PPL = TileMap<TW, TH>::PPL;
     if (rp.eval_stats)
-        hipLaunchKernelGGL((k_render_fwd_stats<TW, TH, LAZY>), dim3(slots), dim3(64), 0, st, rec, ids, c->tranges,
+        hipLaunchKernelGGL((k_render_fwd<TW, TH, true, LAZY>), dim3(slots), dim3(64), 0, st, rec, ids, c->tranges,
+                           order, vt, rp, bg, rgb, T_final, last, c->tile_contrib, c->tile_entries,
+                           c->tile_evals, mode, src);
+    else if (!by_parts(c->n_tiles, (int64_t)c->bin_V * c->bin_N))
+        hipLaunchKernelGGL((k_render_fwd<TW, TH, false, LAZY>), dim3(slots), dim3(64), 0, st, rec, ids, c->tranges,
                            order, vt, rp, bg, rgb, T_final, last, c->tile_contrib, c->tile_entries,
                            c->tile_evals, mode, src);
     else
