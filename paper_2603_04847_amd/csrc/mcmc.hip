@@ -176,22 +176,33 @@ __global__ __launch_bounds__(kBlock) void k_mc_draw(const float* __restrict__ lo
     list[bdead[blockIdx.x] + threadIdx.x] = make_int2(d, s);
 }
 
+// Below one dead in a hundred the moments are cleared by the list of the dead
+// instead of the words of what moved: 5M Gaussians, us a call by the list and by
+// the words, at 0.05% dead 176 and 422, 0.5% 494 and 588, 1% 789 and 771, 2%
+// 1279 and 1164.
+__device__ __forceinline__ bool few_dead(int n, int N) { return (int64_t)100 * n < N; }
+
 // Sources: the opacity and scale of their n copies,
 //   o' = 1 - (1 - o)^(1/n),  scale *= o / sum_{i=1..n} sum_{k<i} C(i-1, k) (-1)^k o'^(k+1) / sqrt(k+1),
 // the double sum taken as sum_{k<n} C(n, k+1) (-1)^k o'^(k+1) / sqrt(k+1) (the
 // binomials sum up a diagonal, and are exact in double to n = 51).  Per 64
-// items, a word of which of them moved (dead or source).
+// items, a word of which of them moved (dead or source), where k_mc_zero reads it.
 __global__ __launch_bounds__(kBlock) void k_mc_sources(float* __restrict__ logit, float* __restrict__ ls, int N,
                                                        const uint32_t* __restrict__ count,
                                                        const int32_t* __restrict__ src,
+                                                       const uint64_t* __restrict__ n_dead,
                                                        uint64_t* __restrict__ moved) {
+    const int nd = (int)*n_dead;
+    if (nd == 0) return;  // uniform over the launch
     __shared__ int s_list[kBlock], s_n[kBlock / kWave];
     __shared__ double s_rs[kMaxCopies];
     const int i0 = blockIdx.x * kBlock, i = i0 + threadIdx.x;
     if (threadIdx.x < kMaxCopies) s_rs[threadIdx.x] = rsqrt((double)(threadIdx.x + 1));
     const bool source = i < N && count[i] != 0u;
-    const uint64_t mv = __ballot(source || (i < N && src[i] >= 0));
-    if (threadIdx.x % kWave == 0 && i < N) moved[i / kWave] = mv;
+    if (!few_dead(nd, N)) {
+        const uint64_t mv = __ballot(source || (i < N && src[i] >= 0));
+        if (threadIdx.x % kWave == 0 && i < N) moved[i / kWave] = mv;
+    }
     const int ns = block_list(source, s_list, s_n);
     if ((int)threadIdx.x >= ns) return;
     const int j = i0 + s_list[threadIdx.x];
@@ -219,7 +230,12 @@ __global__ __launch_bounds__(kBlock) void k_mc_sources(float* __restrict__ logit
 // from it and the partial lines written.  5M Gaussians, a fifth dead, 59 rows,
 // us by the rows a thread takes together: 1 1218, 2 1263, 4 1289, 8 1303, 16
 // 1312, all 1742; a thread per Gaussian, dead or not, walking all rows and then
-// the moments' took 2975.
+// the moments' took 2975.  A row's workgroups cost a launch with few or no dead
+// 0.2 ns each whatever they find: us with none and with a fifth dead, by
+// workgroups a row, 256 5 and 1354, 512 8 and 1320, 1024 14 and 1271, 2048 27 and
+// 1218.
+constexpr unsigned kCopyBlocks = 512;
+
 __global__ __launch_bounds__(256) void k_mc_copy(Rows<kMaxRows> rows, const int2* __restrict__ list,
                                                  const uint64_t* __restrict__ n_dead) {
     const int n = (int)*n_dead;
@@ -231,12 +247,28 @@ __global__ __launch_bounds__(256) void k_mc_copy(Rows<kMaxRows> rows, const int2
 }
 
 // The moments of everything that moved restart at zero.  Bound by the partial
-// lines written (37% of the words at random: every line): 5M Gaussians, 118 rows
-// 916 us, a row after another; 967 eight rows to a thread.
+// lines written (37% of the words at random: every line): 5M Gaussians, 118 rows,
+// a fifth dead 971 us with 256 workgroups a row, 8 with none dead; a thread per
+// item 916 and 489, which made a call with none dead four times as long.
+constexpr unsigned kZeroBlocks = 256;
+
 __global__ __launch_bounds__(256) void k_mc_zero(Rows<2 * kMaxRows> rows, int N,
-                                                 const uint64_t* __restrict__ moved) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < N && (moved[i / kWave] >> (i % kWave) & 1)) rows.p[blockIdx.y][i] = 0.f;
+                                                 const uint64_t* __restrict__ moved,
+                                                 const int2* __restrict__ list,
+                                                 const uint64_t* __restrict__ n_dead) {
+    const int n = (int)*n_dead;
+    float* row = rows.p[blockIdx.y];
+    const int first = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
+    if (few_dead(n, N)) {
+        for (int e = first; e < n; e += step) {
+            const int2 ds = list[e];
+            row[ds.x] = 0.f;
+            row[ds.y] = 0.f;
+        }
+        return;
+    }
+    for (int i = first; i < N; i += step)
+        if (moved[i / kWave] >> (i % kWave) & 1) row[i] = 0.f;
 }
 
 // mu += scale sigmoid(-k (o - t)) Sigma eta
@@ -307,10 +339,12 @@ hipError_t launch_mcmc_relocate(Ctx* c, const gs_gaussian_adam* state, int N, in
     hipLaunchKernelGGL(k_mc_block_offsets, dim3(1), tb, 0, st, bsum, bdead, nb, n_moved);
     hipLaunchKernelGGL(k_mc_draw, gb, tb, 0, st, par.p[10], N, t_dead, u, cdf, bsum, bdead, nb, src, count,
                        list);
-    hipLaunchKernelGGL(k_mc_sources, gb, tb, 0, st, par.p[10], par.p[3], N, count, src, moved);
+    hipLaunchKernelGGL(k_mc_sources, gb, tb, 0, st, par.p[10], par.p[3], N, count, src, bdead + nb,
+                       moved);
     const unsigned g = (unsigned)((N + 255) / 256);
-    hipLaunchKernelGGL(k_mc_copy, dim3(std::min(g, 2048u), par.n), dim3(256), 0, st, par, list, bdead + nb);
-    hipLaunchKernelGGL(k_mc_zero, dim3(g, mom.n), dim3(256), 0, st, mom, N, moved);
+    hipLaunchKernelGGL(k_mc_copy, dim3(std::min(g, kCopyBlocks), par.n), dim3(256), 0, st, par, list, bdead + nb);
+    hipLaunchKernelGGL(k_mc_zero, dim3(std::min(g, kZeroBlocks), mom.n), dim3(256), 0, st, mom, N, moved, list,
+                       bdead + nb);
     return hipGetLastError();
 }
 
