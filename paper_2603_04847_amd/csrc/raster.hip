@@ -621,6 +621,9 @@ __global__ __launch_bounds__(64) void k_render_fwd_part(const float4* __restrict
     TM::pixel(lane, part, x, y);
     const int px = tx * TW + x, py = ty * TH + y;
     const float fx = px + 0.5f, fy = py + 0.5f;
+    // a part outside the view meets no entry and would look through the whole
+    // list for one
+    if (__ballot(px < W && py < H) == 0) return;
     // alpha_min while the pixel composites, 2 once it has stopped (or outside)
     float gmin = (px < W && py < H) ? amin : 2.f;
     float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
