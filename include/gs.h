@@ -134,10 +134,10 @@ typedef struct {
     int32_t lazy_lists;       /* 0: gs_bin_sort writes every tile list in full;
                                  1: it stops at the per-block lists and the tile list
                                  lengths, and gs_render_fwd draws each tile's list from
-                                 its block's list, writing the part it reads (to the
-                                 end of the block entries loaded when the tile's last
-                                 pixel stopped) to the tile lists.  The backward reads no further than that
-                                 part; run without a forward since the bin step, it first
+                                 its block's list, writing the part it reads (at least
+                                 to the entry at which the tile's last pixel stopped)
+                                 to the tile lists.  The backward reads no further than
+                                 that part; run without a forward since the bin step, it first
                                  writes the lists in full.  Images and gradients are the
                                  same bit for bit; only the unread list tails are left
                                  unwritten */
@@ -363,7 +363,11 @@ gs_status gs_init_gaussians(gs_ctx* ctx, const float* points, const float* rgb, 
  * gradients preconditioned with its inverse 6x6 diagonal blocks, in double,
  * for max_iter iterations or until the residual is below tol times the
  * right-hand side (a device flag ends the iteration: the call stays
- * graph-capturable).  The step is to be applied as T_i <- Exp(d_twist_i) T_i
+ * graph-capturable).  The sums over observations run in no fixed order: the
+ * same step taken twice agrees to the rounding of double, which shows in the
+ * last place of a few output floats in a million, and could show in the number
+ * of iterations where a residual falls on the tolerance.  The step is to be
+ * applied as T_i <- Exp(d_twist_i) T_i
  * (gs_pose_compose) and X_k <- X_k + d_X_k.
  * X[Pt][3], viewmat[n_cams][12], intr[n_cams][4]; observations SORTED BY
  * CAMERA (otherwise stats[4] = 1 and the step is zero); pt_off / pt_obs: the

@@ -499,10 +499,6 @@ __global__ __launch_bounds__(kBlock) void k_tile_ranges(const uint32_t* __restri
     (void)TH;
 }
 
-// Per chunk and sub-tile q, the place in q's list of the chunk's first entry
-// of q, for the block of the chunk's first entry: tbase of that block plus the
-// chunk prefix (cb[16 c + q]).  Chunks whose entries all lie in that block
-// (nearly all) need nothing else.
 // The block of the sorted entry j from the blocks' ends (which never fall), the
 // first search over all of them, the second upwards from block B; NB past the last.
 __device__ __forceinline__ uint32_t block_of(const int32_t* __restrict__ branges, uint32_t NB, int64_t j) {
@@ -520,7 +516,11 @@ __device__ __forceinline__ uint32_t block_from(const int32_t* __restrict__ brang
     return B;
 }
 
-// bkey: the sorted entries' block ids, or null and then branges is searched
+// Per chunk and sub-tile q, the place in q's list of the chunk's first entry
+// of q, for the block of the chunk's first entry: tbase of that block plus the
+// chunk prefix (cb[16 c + q]).  Chunks whose entries all lie in that block
+// (nearly all) need nothing else.  bkey: the sorted entries' block ids, or null
+// and then branges is searched.
 __global__ __launch_bounds__(kBlock) void k_chunk_bases(const uint32_t* __restrict__ bkey,
                                                         const int32_t* __restrict__ branges,
                                                         const uint32_t* __restrict__ used,

@@ -513,6 +513,12 @@ __global__ __launch_bounds__(kBlock) void k_project_bwd_color(gs_gaussians g, co
         if (s_acc[k] != 0.0) atomicAdd(&twist_acc[k], s_acc[k]);
 }
 
+// Bound by its arithmetic in double.  The covariance chain runs once for each
+// view, through R Rq in float.  Summed in world axes over the views and run once
+// a Gaussian it takes 400 us instead of 475 (3M Gaussians in 8 views), 460
+// instead of 495 (5M in 4 with Adam), and rounds R Rq less; but it moves single
+// entries of needle-like splats' scale and quaternion gradients by up to 7e-4 of
+// the gradient's rms, where two runs are 3e-4 apart.
 template <bool ADAM>
 __global__ __launch_bounds__(kBlock) void k_project_bwd_geom(gs_gaussians g, const float* __restrict__ viewmat,
                                  const float* __restrict__ intr, ViewTable vt, RasterParams rp,
