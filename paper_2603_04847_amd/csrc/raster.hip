@@ -380,9 +380,9 @@ __global__ __launch_bounds__(64) void k_render_fwd(const float4* __restrict__ re
 // A splat's tiles add their sums by float atomics, so the order the tiles run in
 // decides how its gradient rounds; and a needle-like splat's conic gradients
 // cancel when the projection backward turns them into its scales and rotation,
-// which puts single entries of those up to 2e-3 of the gradient's rms apart
-// between two orders (4 x 1600x1066, 5M splats, where two runs in one order
-// are 5e-4 apart).  So the tiles run neither heaviest first by what they walk nor
+// which puts single entries of those 1e-3 to 2e-3 of the gradient's rms apart
+// between two orders (4 x 1600x1066, 5M splats), two to three times as far as
+// two runs in one order mostly are.  So the tiles run neither heaviest first by what they walk nor
 // cut into waves that walk a list's segments at once, though both are faster:
 // us for this, and for those, on 4 x 1237x822 890 and 680, on 4 x 1600x1066 1665
 // and 1080, on one 256x256 view 146 and 91; on 8 uneven views 1120 and 1145.
